@@ -19,6 +19,7 @@
 #include "eig.h"
 #include "fused.h"
 #include "gemm3.h"
+#include "modepass.h"
 #include "grad.h"
 #include "op.h"
 #include "resident.h"
@@ -132,9 +133,11 @@ int32_t ensure_ws(cola_op_s* op, int nrhs, hipStream_t st) {
 
 // ---------------------------------------------------------------------------
 // tile choice: table entry (autotuned) or a size-based default
-TileCfg tile_for(const cola_op_s* op, int prec, bool rows, int64_t nk, int64_t B, int64_t g) {
+TileCfg tile_for(const cola_op_s* op, int prec, bool rows, int64_t nk, int64_t B, int64_t g, int64_t nrhs, int nout) {
     auto it = op->tiles.find(PassKey{prec, rows ? 1 : 0, nk, B, g});
     if (it != op->tiles.end()) return it->second;
+    if (prec == COLA_PREC_FP64 || prec == COLA_PREC_FP32)
+        return rows ? mode_tile(true, nk, nrhs * g, nk, nout) : mode_tile(false, nk, nk, B, nrhs * g * nout);
     if (rows) {
         const int wn = nk >= 64 ? 2 : 1;
         const int wm = g >= 8192 ? 4 : 2;
@@ -455,7 +458,7 @@ int32_t enqueue_mvm(cola_op_s* op, const SysInfo& s, int prec, int nrhs, const v
             kname = prec == COLA_PREC_FP64 ? (rows ? "contract_rows_fp64" : "contract_mid_fp64")
                                            : (rows ? "contract_rows" : "contract_mid");
         }
-        TileCfg cfg = tile_for(op, prec, rows, nk, a.B, a.a_per_rhs);
+        TileCfg cfg = tile_for(op, prec, rows, nk, a.B, a.a_per_rhs, nrhs, a.nout);
         {
             ProfScope ps(prof, kname, st);
             HIP_TRY(launch_contract(prec, rows, a, cfg, st));
@@ -1404,7 +1407,8 @@ int32_t cola_op_create(const cola_system_desc* systems, int32_t nsys, int32_t pr
         if (s.Fv != 2 || s.J != 1 || s.dims[0] > kSmallMax || s.dims[1] > kSmallMax) small_ok = false;
     (void)hipDeviceGetAttribute(&op->num_cus, hipDeviceAttributeMultiprocessorCount, op->device);
 
-    int32_t rc = dev_alloc(op, (void**)&op->fac64, sizeof(double) * fac);
+    // factors are padded by 128 bytes: the mode products' loads of a last row may run past its end
+    int32_t rc = dev_alloc(op, (void**)&op->fac64, sizeof(double) * (fac + 16));
     if (rc == COLA_OK && dg > 0) rc = dev_alloc(op, (void**)&op->diag64, sizeof(double) * dg);
     if (rc != COLA_OK) {
         cola_op_destroy(op);
@@ -1441,7 +1445,7 @@ int32_t cola_op_create(const cola_system_desc* systems, int32_t nsys, int32_t pr
     op->small_ok = small_ok && build_small(op) == COLA_OK;
     // working copies
     if (prec != COLA_PREC_FP64) {
-        rc = dev_alloc(op, (void**)&op->fac32, sizeof(float) * fac);
+        rc = dev_alloc(op, (void**)&op->fac32, sizeof(float) * (fac + 32));
         if (rc == COLA_OK && dg > 0) rc = dev_alloc(op, (void**)&op->diag32, sizeof(float) * dg);
         if (rc == COLA_OK && (prec == COLA_PREC_BF16 || prec == COLA_PREC_BF16X3)) {
             op->nsplit = (prec == COLA_PREC_BF16) ? 1 : 3;

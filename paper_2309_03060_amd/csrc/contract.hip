@@ -1,4 +1,5 @@
-// Mode contraction pass of the Kronecker MVM on gfx950 matrix cores.
+// Mode contraction pass of the Kronecker MVM on gfx950 matrix cores: the BF16 policies, and the
+// dispatch of FP64 and FP32 passes to the mode products of modepass.hip.
 //
 // A Kronecker term applied to x (row-major vec) multiplies every tensor mode
 // of X = x.reshape(n1, .., nF) by its factor; the MVM cost of Table 2
@@ -11,7 +12,7 @@
 //
 // Operands are staged in LDS as [row][k] tiles (k contiguous) and fed to
 // 16x16 MFMA tiles; each of the 4 waves owns a (16*WM) x (16*WN) sub-tile.
-// Precision policies: FP64 (v_mfma_f64_16x16x4f64), FP32 (v_mfma_f32_16x16x4f32),
+// Precision policies:
 // BF16 (v_mfma_f32_16x16x32_bf16, FP32 accumulation) and BF16x3 (each operand
 // split into three bf16 parts; the six leading cross products are summed).
 //
@@ -19,19 +20,12 @@
 // (the diagonal term of the Sum, the search-direction update and the partial
 // dot product p.Ap) or of the FP64 refinement residual r = b - A x.
 #include "contract.h"
+#include "modepass.h"
 
 namespace cola {
 
 // ----------------------------------------------------------------------------
 // precision policies
-struct PolF64 {
-    using V = double; using Fac = double; using L = double; using Acc = doublex4;
-    static constexpr int KT = 16, KSTEP = 4, NS = 1, KP = KT + 2;
-};
-struct PolF32 {
-    using V = float; using Fac = float; using L = float; using Acc = floatx4;
-    static constexpr int KT = 32, KSTEP = 4, NS = 1, KP = KT + 4;
-};
 struct PolBF16 {
     using V = float; using Fac = __bf16; using L = __bf16; using Acc = floatx4;
     static constexpr int KT = 32, KSTEP = 32, NS = 1, KP = KT + 8;
@@ -41,16 +35,6 @@ struct PolBF16X3 {
     static constexpr int KT = 32, KSTEP = 32, NS = 3, KP = KT + 8;
 };
 
-template <class P> struct IsBf { static constexpr bool value = false; };
-template <> struct IsBf<PolBF16> { static constexpr bool value = true; };
-template <> struct IsBf<PolBF16X3> { static constexpr bool value = true; };
-
-__device__ inline floatx4 mma(float a, float b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ inline doublex4 mma(double a, double b, doublex4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
 __device__ inline floatx4 mma(bf16x8 a, bf16x8 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -58,18 +42,14 @@ __device__ inline floatx4 mma(bf16x8 a, bf16x8 b, floatx4 c) {
 // Split a working-precision value into the policy's LDS parts.
 template <class P>
 __device__ inline void split_value(typename P::V v, typename P::L* out) {
-    if constexpr (!IsBf<P>::value) {
-        out[0] = v;
-    } else {
-        __bf16 h = (__bf16)v;                  // round to nearest even
-        out[0] = h;
-        if constexpr (P::NS == 3) {
-            float r1 = v - (float)h;
-            __bf16 m = (__bf16)r1;
-            float r2 = r1 - (float)m;
-            out[1] = m;
-            out[2] = (__bf16)r2;
-        }
+    __bf16 h = (__bf16)v;                      // round to nearest even
+    out[0] = h;
+    if constexpr (P::NS == 3) {
+        float r1 = v - (float)h;
+        __bf16 m = (__bf16)r1;
+        float r2 = r1 - (float)m;
+        out[1] = m;
+        out[2] = (__bf16)r2;
     }
 }
 
@@ -82,44 +62,28 @@ __device__ inline void load4(const float* p, float* o) {
     const floatx4 v = *(const floatx4*)p;
     o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
 }
-__device__ inline void load4(const double* p, double* o) {
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    const d2 a = *(const d2*)p, b = *(const d2*)(p + 2);
-    o[0] = a[0]; o[1] = a[1]; o[2] = b[0]; o[3] = b[1];
-}
 __device__ inline void load4(const __bf16* p, __bf16* o) {
     typedef __bf16 b4 __attribute__((ext_vector_type(4)));
     const b4 v = *(const b4*)p;
     o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
 }
 __device__ inline void store4(float* p, const float* v) { *(floatx4*)p = floatx4{v[0], v[1], v[2], v[3]}; }
-__device__ inline void store4(double* p, const double* v) {
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    *(d2*)p = d2{v[0], v[1]};
-    *(d2*)(p + 2) = d2{v[2], v[3]};
-}
 
 template <class P, int WM, int WN, bool ROWS>
 __global__ __launch_bounds__(kThreads) void k_contract(PassArgs a) {
     using V = typename P::V; using Fac = typename P::Fac; using L = typename P::L;
     using Acc = typename P::Acc;
     constexpr int MT = 32 * WM, NT = 32 * WN, KT = P::KT, KP = P::KP, NS = P::NS;
-    constexpr int EPAD = sizeof(V) == 8 ? 2 : 4;
+    constexpr int EPAD = 4;
     constexpr int EW = 16 * WN + EPAD;                       // epilogue row stride (elements)
-    // COLS, FP32/FP64: the vector tile is staged as [k][n] (as it lies in
-    // memory) with a row pitch of 16 (mod 64) banks, which keeps both the
-    // 16-byte staging writes and the MFMA operand reads free of bank
-    // conflicts; the bf16 policies keep [n][k] for their 8-wide k operands.
-    constexpr bool BKN = !ROWS && !IsBf<P>::value;
-    constexpr int NTP = NT + (sizeof(L) == 8 ? 8 : 16);
-    constexpr size_t B_ELEMS = BKN ? (size_t)KT * NTP : (size_t)NT * KP;
+    constexpr size_t B_ELEMS = (size_t)NT * KP;
     constexpr size_t AB_BYTES = sizeof(L) * NS * ((size_t)MT * KP + B_ELEMS);
     constexpr size_t E_BYTES = sizeof(V) * 4 * 16 * (size_t)EW;
     constexpr size_t SMEM = AB_BYTES > E_BYTES ? AB_BYTES : E_BYTES;
     __shared__ __attribute__((aligned(16))) char smem[SMEM];
     __shared__ double red[4];
     L* As = (L*)smem;                      // [NS][MT][KP]
-    L* Bs = As + NS * MT * KP;             // [NS][NT][KP], or [KT][NTP] when BKN
+    L* Bs = As + NS * MT * KP;             // [NS][NT][KP]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -256,31 +220,6 @@ __global__ __launch_bounds__(kThreads) void k_contract(PassArgs a) {
             } else {
                 // A: factor rows K[i, k], B: vector X[g, k, b] (b contiguous) stored as [b][k]
                 stage_factor(As, Kp, m0, MT, k0);
-                if (BKN && tile_full && k0 + KT <= nk) {
-                    // whole tile in range: straight-line 16-byte loads, all issued before use
-                    constexpr int NE = (KT * (NT / 4) + kThreads - 1) / kThreads;
-                    V v[NE][4], rr4[NE][4];
-#pragma unroll
-                    for (int q = 0; q < NE; ++q) {
-                        const int e = tid + kThreads * q;
-                        if (e < KT * (NT / 4)) {
-                            const int k = e / (NT / 4), n = (e % (NT / 4)) * 4;
-                            const int64_t idx = (g * nk + k0 + k) * a.B + n0 + n;
-                            load4(Xp + idx, v[q]);
-                            if (a.pnew) load4(Rp + idx, rr4[q]);
-                        }
-                    }
-#pragma unroll
-                    for (int q = 0; q < NE; ++q) {
-                        const int e = tid + kThreads * q;
-                        if (e < KT * (NT / 4)) {
-                            const int k = e / (NT / 4), n = (e % (NT / 4)) * 4;
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                Bs[k * NTP + n + c] = (L)(a.pnew ? pnew_of(rr4[q][c], v[q][c], beta_blk) : v[q][c]);
-                        }
-                    }
-                } else
                 for (int e = tid; e < KT * (NT / 4); e += kThreads) {
                     const int k = e / (NT / 4), n = (e % (NT / 4)) * 4;
                     const int gk = k0 + k;
@@ -305,17 +244,12 @@ __global__ __launch_bounds__(kThreads) void k_contract(PassArgs a) {
                                 }
                         }
                     }
-                    if constexpr (BKN) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) Bs[k * NTP + n + c] = (L)v[c];
-                    } else {
+                    for (int c = 0; c < 4; ++c) {
+                        L parts[NS];
+                        split_value<P>(v[c], parts);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            L parts[NS];
-                            split_value<P>(v[c], parts);
-#pragma unroll
-                            for (int sp = 0; sp < NS; ++sp) Bs[(sp * NT + n + c) * KP + k] = parts[sp];
-                        }
+                        for (int sp = 0; sp < NS; ++sp) Bs[(sp * NT + n + c) * KP + k] = parts[sp];
                     }
                 }
             }
@@ -323,50 +257,34 @@ __global__ __launch_bounds__(kThreads) void k_contract(PassArgs a) {
             // ---- MFMA over the staged K slice ----
 #pragma unroll
             for (int kk = 0; kk < KT; kk += P::KSTEP) {
-                if constexpr (!IsBf<P>::value) {
-                    L av[WM], bv[WN];
+                bf16x8 av[NS][WM], bv[NS][WN];
+#pragma unroll
+                for (int sp = 0; sp < NS; ++sp) {
 #pragma unroll
                     for (int i = 0; i < WM; ++i)
-                        av[i] = As[(wm * WM * 16 + i * 16 + (lane & 15)) * KP + kk + (lane >> 4)];
+                        av[sp][i] = *(const bf16x8*)&As[(sp * MT + wm * WM * 16 + i * 16 + (lane & 15)) * KP + kk +
+                                                       8 * (lane >> 4)];
+#pragma unroll
+                    for (int j = 0; j < WN; ++j)
+                        bv[sp][j] = *(const bf16x8*)&Bs[(sp * NT + wn * WN * 16 + j * 16 + (lane & 15)) * KP + kk +
+                                                       8 * (lane >> 4)];
+                }
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
 #pragma unroll
                     for (int j = 0; j < WN; ++j) {
-                        if constexpr (BKN) bv[j] = Bs[(kk + (lane >> 4)) * NTP + wn * WN * 16 + j * 16 + (lane & 15)];
-                        else bv[j] = Bs[(wn * WN * 16 + j * 16 + (lane & 15)) * KP + kk + (lane >> 4)];
-                    }
-#pragma unroll
-                    for (int i = 0; i < WM; ++i)
-#pragma unroll
-                        for (int j = 0; j < WN; ++j) acc[i][j] = mma(av[i], bv[j], acc[i][j]);
-                } else {
-                    bf16x8 av[NS][WM], bv[NS][WN];
-#pragma unroll
-                    for (int sp = 0; sp < NS; ++sp) {
-#pragma unroll
-                        for (int i = 0; i < WM; ++i)
-                            av[sp][i] = *(const bf16x8*)&As[(sp * MT + wm * WM * 16 + i * 16 + (lane & 15)) * KP + kk +
-                                                           8 * (lane >> 4)];
-#pragma unroll
-                        for (int j = 0; j < WN; ++j)
-                            bv[sp][j] = *(const bf16x8*)&Bs[(sp * NT + wn * WN * 16 + j * 16 + (lane & 15)) * KP + kk +
-                                                           8 * (lane >> 4)];
-                    }
-#pragma unroll
-                    for (int i = 0; i < WM; ++i)
-#pragma unroll
-                        for (int j = 0; j < WN; ++j) {
-                            if constexpr (NS == 1) {
-                                acc[i][j] = mma(av[0][i], bv[0][j], acc[i][j]);
-                            } else {
-                                // smallest products first: lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi
-                                acc[i][j] = mma(av[2][i], bv[0][j], acc[i][j]);
-                                acc[i][j] = mma(av[0][i], bv[2][j], acc[i][j]);
-                                acc[i][j] = mma(av[1][i], bv[1][j], acc[i][j]);
-                                acc[i][j] = mma(av[1][i], bv[0][j], acc[i][j]);
-                                acc[i][j] = mma(av[0][i], bv[1][j], acc[i][j]);
-                                acc[i][j] = mma(av[0][i], bv[0][j], acc[i][j]);
-                            }
+                        if constexpr (NS == 1) {
+                            acc[i][j] = mma(av[0][i], bv[0][j], acc[i][j]);
+                        } else {
+                            // smallest products first: lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi
+                            acc[i][j] = mma(av[2][i], bv[0][j], acc[i][j]);
+                            acc[i][j] = mma(av[0][i], bv[2][j], acc[i][j]);
+                            acc[i][j] = mma(av[1][i], bv[1][j], acc[i][j]);
+                            acc[i][j] = mma(av[1][i], bv[0][j], acc[i][j]);
+                            acc[i][j] = mma(av[0][i], bv[1][j], acc[i][j]);
+                            acc[i][j] = mma(av[0][i], bv[0][j], acc[i][j]);
                         }
-                }
+                    }
             }
             __syncthreads();
         }
@@ -588,8 +506,8 @@ static hipError_t launch_p(bool rows, const PassArgs& a, TileCfg c, hipStream_t 
 
 hipError_t launch_contract(int prec, bool rows, const PassArgs& a, TileCfg cfg, hipStream_t s) {
     switch (prec) {
-        case COLA_PREC_FP64:   return launch_p<PolF64>(rows, a, cfg, s);
-        case COLA_PREC_FP32:   return launch_p<PolF32>(rows, a, cfg, s);
+        case COLA_PREC_FP64:
+        case COLA_PREC_FP32:   return launch_mode_pass(prec, rows, a, cfg, s);
         case COLA_PREC_BF16:   return launch_p<PolBF16>(rows, a, cfg, s);
         case COLA_PREC_BF16X3: return launch_p<PolBF16X3>(rows, a, cfg, s);
         default: return hipErrorInvalidValue;

@@ -20,6 +20,7 @@
 
 #include "gemm.h"
 #include "gemm3.h"
+#include "modepass.h"
 #include "vector.h"
 
 namespace cola {
@@ -175,8 +176,7 @@ int32_t apply_modes_f64(cola_op_s* op, const SysInfo& s, int term, int skip, con
         a.G = (int64_t)nrhs * lead;
         a.B = rows ? 1 : trail;
         a.a_per_rhs = lead;
-        TileCfg cfg{nk >= 64 ? 2 : 1, rows ? (nk >= 64 ? 2 : 1) : (trail >= 64 ? 2 : 1)};
-        if (rows) cfg.wm = 2;
+        const TileCfg cfg = rows ? mode_tile(true, nk, a.G, nk, 1) : mode_tile(false, nk, nk, trail, a.G);
         if (launch_contract(COLA_PREC_FP64, rows, a, cfg, st) != hipSuccess) return COLA_ERR_HIP;
         in = bufs[cur];
         cur ^= 1;
