@@ -110,7 +110,7 @@ int32_t ensure_ws(cola_op_s* op, int nrhs, hipStream_t st) {
     rc |= dev_alloc(op, (void**)&w.b64, vec);
     w.part_stride = max_blocks_per_rhs(op);
     rc |= dev_alloc(op, (void**)&w.partials, sizeof(double) * (size_t)nrhs * w.part_stride);
-    rc |= dev_alloc(op, (void**)&w.counters, sizeof(uint32_t) * (size_t)nrhs);
+    rc |= dev_alloc(op, (void**)&w.counters, sizeof(uint32_t) * (size_t)nrhs * kCounterStride);
     rc |= dev_alloc(op, (void**)&w.cg, sizeof(CgState) * (size_t)nrhs);
     rc |= dev_alloc(op, (void**)&w.outer, sizeof(OuterState) * (size_t)nrhs);
     rc |= dev_alloc(op, (void**)&w.cnt, sizeof(SolveCounters));
@@ -124,7 +124,7 @@ int32_t ensure_ws(cola_op_s* op, int nrhs, hipStream_t st) {
         return COLA_ERR_OOM;
     }
     w.nrhs = nrhs;
-    HIP_TRY(fill_i32((int32_t*)w.counters, 0, nrhs, st));
+    HIP_TRY(fill_i32((int32_t*)w.counters, 0, (int64_t)nrhs * kCounterStride, st));
     HIP_TRY(fill_i32((int32_t*)w.cnt, 0, 2, st));
     HIP_TRY(fill_i32((int32_t*)w.cg, 0, (int64_t)nrhs * sizeof(CgState) / 4, st));
     HIP_TRY(fill_i32((int32_t*)w.outer, 0, (int64_t)nrhs * sizeof(OuterState) / 4, st));

@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kThreads) void k_contract(PassArgs a) {
             const int64_t nblk = nBt * nMt;
             const int64_t myb = (blockIdx.x % nBt) + nBt * (blockIdx.y % nMt);
             double tot;
-            if (last_block_reduce(s, a.partials + g * a.part_stride, a.counters + g, (int)nblk,
+            if (last_block_reduce(s, a.partials + g * a.part_stride, a.counters + g * kCounterStride, (int)nblk,
                                   (int)myb, &tot, red) && tid == 0) {
                 if (a.epi == EPI_CG) {
                     CgState& st = a.cg[g];

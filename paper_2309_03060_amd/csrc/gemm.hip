@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kGT) void k_gemm2_y(Gemm2Args a) {
     if (!cg) return;
     const double s = block_sum8(dot, red);
     double tot;
-    if (last_block_reduce8(s, a.partials + (int64_t)r * a.part_stride, a.counters + r, tpr, t, &tot, red) &&
+    if (last_block_reduce8(s, a.partials + (int64_t)r * a.part_stride, a.counters + (int64_t)r * kCounterStride, tpr, t, &tot, red) &&
         threadIdx.x == 0) {
         CgState& st = a.cg[r];
         if (!(tot > 0.0) || !finite_d(tot)) {
@@ -482,7 +482,7 @@ __device__ inline void g64_finish(const Gemm64Args& a, int r, int tpr, int t, do
     if (epi != EPI_CG && epi != EPI_RESID && epi != EPI_RESID_CG) return;
     const double s = block_sum8(dot, red);
     double tot;
-    if (last_block_reduce8(s, a.partials + (int64_t)r * a.part_stride, a.counters + r, tpr, t, &tot, red) &&
+    if (last_block_reduce8(s, a.partials + (int64_t)r * a.part_stride, a.counters + (int64_t)r * kCounterStride, tpr, t, &tot, red) &&
         threadIdx.x == 0) {
         if (epi == EPI_CG) {
             CgState& st = a.cg[r];

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm3(Gemm3Args a, PassDesc d) {
         const int tpr = (int)(d.rows_per_rhs / BM) * Nt;
         const int t = (int)((m0 - (int64_t)r * d.rows_per_rhs) / BM) * Nt + nt;
         double tot;
-        if (last_block_reduce(sum, a.partials + (int64_t)r * a.part_stride, a.counters + r, tpr, t, &tot, red) &&
+        if (last_block_reduce(sum, a.partials + (int64_t)r * a.part_stride, a.counters + (int64_t)r * kCounterStride, tpr, t, &tot, red) &&
             threadIdx.x == 0) {
             CgState& st = a.cg[r];
             st.xlag = 0;                                   // the first pass has caught x up
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(XT) void k_gemm3x3(Gemm3Args a, PassDesc d) {
         const int tpr = (int)(d.rows_per_rhs / BM) * Nt;
         const int t = (int)((m0 - (int64_t)r * d.rows_per_rhs) / BM) * Nt + nt;
         double tot;
-        if (last_block_reduce8(sum, a.partials + (int64_t)r * a.part_stride, a.counters + r, tpr, t, &tot, red) &&
+        if (last_block_reduce8(sum, a.partials + (int64_t)r * a.part_stride, a.counters + (int64_t)r * kCounterStride, tpr, t, &tot, red) &&
             threadIdx.x == 0) {
             CgState& st = a.cg[r];
             st.xlag = 0;                                   // the first pass has caught x up

@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
         if (epi == EPI_CG || epi == EPI_RESID || epi == EPI_RESID_CG) {
             const double s = block_sum(dot, red);
             double tot;
-            if (last_block_reduce(s, a.partials + g * a.part_stride, a.counters + g, (int)(nNt * nMt),
+            if (last_block_reduce(s, a.partials + g * a.part_stride, a.counters + g * kCounterStride, (int)(nNt * nMt),
                                   (int)(nt + nNt * mt), &tot, red) && tid == 0) {
                 if (epi == EPI_CG) {
                     CgState& st = a.cg[g];

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kThreads) void k_pcg_update(double* x, double* r, c
     }
     s = block_sum(s, red);
     double tot;
-    if (last_block_reduce(s, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(s, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0) {
         CgState& st = cg[g];
         st.iters += 1;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kThreads) void k_pcg_precond_dot(const double* r, d
     }
     s = block_sum(s, red);
     double tot;
-    if (last_block_reduce(s, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(s, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0) {
         CgState& st = cg[g];
         if (!(tot > 0.0) || !finite_d(tot)) {

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kThreads) void k_outer_init(const double* B, double
     }
     s = block_sum(s, red);
     double tot;
-    if (last_block_reduce(s, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(s, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0) {
         OuterState& o = outer[g];
         o.bnorm2 = tot;
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kThreads) void k_cg_prepare(const double* src, T* r
     }
     s = block_sum(s, red);
     double tot;
-    if (last_block_reduce(s, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(s, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0) {
         CgState& st = cg[g];
         st.rho = tot;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void k_rhs_norm2(const double* B, int64_t
         s += bg[i] * bg[i];
     s = block_sum(s, red);
     double tot;
-    if (last_block_reduce(s, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(s, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0)
         cg[g].bnorm2 = tot;
 }
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void k_cg_update(T* x, T* r, const T* p, 
     }
     s = block_sum(s, red);
     double tot;
-    if (last_block_reduce(s, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(s, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0) {
         CgState& st = cg[g];
         st.iters += 1;
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void k_reliable_apply(const double* r64, 
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
         lg[i] = (T)rg[i];
     double tot;
-    if (last_block_reduce(0.0, partials + g * part_stride, counters + g, gridDim.x, blockIdx.x, &tot, red) &&
+    if (last_block_reduce(0.0, partials + g * part_stride, counters + g * kCounterStride, gridDim.x, blockIdx.x, &tot, red) &&
         threadIdx.x == 0) {
         cg[g].xlag = 0;                                  // the fold applied any deferred step
         reliable_finish(cg[g], cnt);
