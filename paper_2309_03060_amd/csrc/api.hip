@@ -1467,7 +1467,8 @@ int32_t cola_op_create(const cola_system_desc* systems, int32_t nsys, int32_t pr
 }
 
 // ---------------------------------------------------------------------------
-// Kronecker-eigen solve: decompose every factor once (FP64 one-sided Jacobi),
+// Kronecker-eigen solve: decompose every factor once (FP64 one-sided Jacobi; the
+// factors that fit a workgroup's LDS all at once),
 // keep the eigenvector factors as two internal operators (Q^T and Q) and the
 // eigenvalues; a solve is then two Kronecker MVMs and one scaling.
 namespace {
@@ -1484,14 +1485,42 @@ int32_t ensure_eig(cola_op_s* op, hipStream_t st) {
             vec_total += s.dims[k] * s.dims[k];
         }
     }
-    double *vt = nullptr, *q = nullptr, *work = nullptr, *off = nullptr;
+    // factors that fit the LDS of a workgroup are decomposed side by side, larger ones one by one
+    int64_t small_total = 0, rot_total = 0;
+    int nsmall = 0, small_max = 1;
+    bool large = false;
+    for (const SysInfo& s : op->sys)
+        for (int k = 0; k < s.Fv; ++k) {
+            const int64_t nk = s.dims[k];
+            if (nk > kJacobiLds) {
+                large = true;
+                continue;
+            }
+            small_total += nk * nk;
+            rot_total += 2 * jacobi_rotations(nk);
+            small_max = std::max(small_max, (int)nk);
+            ++nsmall;
+        }
+    double *vt = nullptr, *q = nullptr, *work = nullptr, *off = nullptr, *u = nullptr;
+    double2* rot = nullptr;
+    JacobiItem* items = nullptr;
+    JacobiState* state = nullptr;
     int32_t rc = dev_alloc(op, (void**)&op->eig_lam, sizeof(double) * lam_total);
     rc |= dev_alloc(op, (void**)&vt, sizeof(double) * vec_total);
     rc |= dev_alloc(op, (void**)&q, sizeof(double) * vec_total);
-    rc |= dev_alloc(op, (void**)&work, sizeof(double) * nmax * nmax);
-    rc |= dev_alloc(op, (void**)&off, sizeof(double) * 2);
+    if (large) {
+        rc |= dev_alloc(op, (void**)&work, sizeof(double) * nmax * nmax);
+        rc |= dev_alloc(op, (void**)&off, sizeof(double) * 2);
+    }
+    if (nsmall > 0) {
+        rc |= dev_alloc(op, (void**)&u, sizeof(double) * small_total);
+        rc |= dev_alloc(op, (void**)&rot, sizeof(double2) * rot_total);
+        rc |= dev_alloc(op, (void**)&items, sizeof(JacobiItem) * nsmall);
+        rc |= dev_alloc(op, (void**)&state, sizeof(JacobiState) * nsmall);
+    }
     auto cleanup = [&]() {
-        for (void* p : {(void*)vt, (void*)q, (void*)work, (void*)off})
+        for (void* p : {(void*)vt, (void*)q, (void*)work, (void*)off, (void*)u, (void*)rot, (void*)items,
+                        (void*)state})
             if (p) dev_free(op, p);
     };
     if (rc != COLA_OK) {
@@ -1503,14 +1532,22 @@ int32_t ensure_eig(cola_op_s* op, hipStream_t st) {
     }
     std::vector<std::array<const void*, 3>> fqt(op->sys.size()), fq(op->sys.size());
     std::vector<cola_system_desc> dqt(op->sys.size()), dq(op->sys.size());
-    int64_t voff = 0;
+    std::vector<JacobiItem> hitems;
+    int64_t voff = 0, uoff = 0, roff = 0;
     for (size_t i = 0; i < op->sys.size() && rc == COLA_OK; ++i) {
         const SysInfo& s = op->sys[i];
         for (int k = 0; k < s.Fv && rc == COLA_OK; ++k) {
             const int64_t nk = s.dims[k];
-            rc = jacobi_eig(op->fac64 + s.fac_off[k], nk, vt + voff, op->eig_lam + op->eig_lam_off[i][k], work,
-                            off, 4e-15, 40, st);
-            if (rc == COLA_OK && transpose_f64(vt + voff, q + voff, nk, st) != hipSuccess) rc = COLA_ERR_HIP;
+            const double* A = op->fac64 + s.fac_off[k];
+            double* lam = op->eig_lam + op->eig_lam_off[i][k];
+            if (nk <= kJacobiLds) {
+                hitems.push_back(JacobiItem{A, u + uoff, q + voff, vt + voff, lam, rot + roff, (int32_t)nk});
+                uoff += nk * nk;
+                roff += 2 * jacobi_rotations(nk);
+            } else {
+                rc = jacobi_eig(A, nk, vt + voff, lam, work, off, 4e-15, 40, st);
+                if (rc == COLA_OK && transpose_f64(vt + voff, q + voff, nk, st) != hipSuccess) rc = COLA_ERR_HIP;
+            }
             fqt[i][k] = vt + voff;             // column-major V is the row-major Q^T
             fq[i][k] = q + voff;
             voff += nk * nk;
@@ -1525,6 +1562,11 @@ int32_t ensure_eig(cola_op_s* op, hipStream_t st) {
         dqt[i].factors = fqt[i].data();
         dq[i].factors = fq[i].data();
     }
+    if (rc == COLA_OK && nsmall > 0 &&
+        hipMemcpyAsync(items, hitems.data(), sizeof(JacobiItem) * nsmall, hipMemcpyHostToDevice, st) != hipSuccess)
+        rc = COLA_ERR_HIP;
+    for (int i0 = 0; i0 < nsmall && rc == COLA_OK; i0 += 65535)          // a grid dimension's limit
+        rc = jacobi_eig_batch(items + i0, state + i0, std::min(65535, nsmall - i0), small_max, 4e-15, 40, st);
     if (rc == COLA_OK) rc = cola_op_create(dqt.data(), (int32_t)dqt.size(), COLA_PREC_FP64, st, &op->eig_qt);
     if (rc == COLA_OK) rc = cola_op_create(dq.data(), (int32_t)dq.size(), COLA_PREC_FP64, st, &op->eig_q);
     (void)hipStreamSynchronize(st);                        // the operators own copies now

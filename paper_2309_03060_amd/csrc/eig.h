@@ -14,6 +14,33 @@ namespace cola {
 int32_t jacobi_eig(const double* A, int64_t n, double* V, double* lam, double* work, double* off,
                    double tol, int max_sweeps, hipStream_t s);
 
+// One factor of a batched decomposition: matrices n x n in FP64, `q` row-major Q (column j =
+// eigenvector j), `vt` row-major Q^T, `u` and `rot` scratch (n * n doubles; rotations of two sweeps).
+struct JacobiItem {
+    const double* A;
+    double* u;
+    double* q;
+    double* vt;
+    double* lam;
+    double2* rot;
+    int32_t n;
+};
+struct JacobiState {
+    int32_t done;        // a sweep found every pair within the tolerance
+    int32_t rotated[2];  // whether the last sweep, and the one before, rotated anything (by sweep mod 2)
+    int32_t pad;
+};
+
+// Largest factor a workgroup holds in LDS (n * n doubles of 160 KB, with room for the rest).
+constexpr int kJacobiLds = 140;
+// Rotations of one sweep: n / 2 pairs (n rounded up to even) in n - 1 steps.
+constexpr int64_t jacobi_rotations(int64_t n) { return (n + (n & 1)) / 2 * (n + (n & 1) - 1); }
+
+// Decompose nitems factors of at most kJacobiLds (device arrays items and state; all symmetric
+// positive semi-definite) side by side.  Waits on the stream every few sweeps.
+int32_t jacobi_eig_batch(const JacobiItem* items, JacobiState* state, int nitems, int nmax, double tol,
+                         int max_sweeps, hipStream_t s);
+
 // Z[r, i1, i2, i3] = Y[r, i1, i2, i3] / (lam1[i1] lam2[i2] lam3[i3] + sigma2) for
 // nrhs packed right-hand sides of one system (F modes, unused dims = 1).
 hipError_t eig_scale(const double* Y, double* Z, int64_t nrhs, int F, const int64_t* dims,

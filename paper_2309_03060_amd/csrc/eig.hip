@@ -11,6 +11,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
+#include <vector>
 
 #include "vector.h"
 
@@ -74,6 +76,189 @@ __global__ void k_jacobi_init(const double* A, double* U, double* V, int64_t n) 
     }
 }
 
+// Sum over the 16 lanes of a DPP row, valid in each of them.
+__device__ inline double row_sum16(double v) {
+    auto add = [](double x, auto ctrl) {
+        constexpr int c = decltype(ctrl)::value;
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, c, 0xf, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), c, 0xf, 0xf, true);
+        return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    };
+    v = add(v, std::integral_constant<int, 0xB1>{});        // lane ^ 1 (quad_perm 1, 0, 3, 2)
+    v = add(v, std::integral_constant<int, 0x4E>{});        // lane ^ 2 (quad_perm 2, 3, 0, 1)
+    v = add(v, std::integral_constant<int, 0x141>{});       // the other quad of eight (row_half_mirror)
+    return add(v, std::integral_constant<int, 0x140>{});    // the other eight (row_mirror)
+}
+
+// One pair of columns of U in LDS by 16 lanes (lane l: rows l, l + 16, ..; R of them): rotate them
+// orthogonal and return the rotation.
+template <int R>
+__device__ inline double2 jacobi_pair(double* up, double* uq, int n, int l, double tol, bool& rotated) {
+    double x[R], y[R];
+    double a = 0.0, b = 0.0, g = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool in = r + 1 < R || l + 16 * r < n;
+        x[r] = in ? up[l + 16 * r] : 0.0;
+        y[r] = in ? uq[l + 16 * r] : 0.0;
+        a = __builtin_fma(x[r], x[r], a);
+        b = __builtin_fma(y[r], y[r], b);
+        g = __builtin_fma(x[r], y[r], g);
+    }
+    a = row_sum16(a);
+    b = row_sum16(b);
+    g = row_sum16(g);
+    // |u_p . u_q| / (|u_p| |u_q|) against the tolerance: a threshold, an approximate root will do
+    const double ab = __builtin_amdgcn_sqrt(a * b);
+    if (!(fabs(g) > tol * ab)) return double2{1.0, 0.0};
+    rotated = true;
+    // t, the smaller root of t^2 + 2 zeta t - 1 = 0 with zeta = d / h, as h / (d + sign(d) |(d, h)|): its
+    // rounding only leaves a little of g for the next sweep, so root and reciprocal are approximate
+    // (v_sqrt_f64, v_rcp_f64 and a Newton step); c is not, so that (c, c t) stays a rotation.
+    double d = b - a, h = 2.0 * g;
+    const double big = fmax(fabs(d), fabs(h));
+    const double scale = big < 0x1p-450 ? 0x1p500 : (big > 0x1p450 ? 0x1p-500 : 1.0);
+    d *= scale;
+    h *= scale;
+    const double e = fabs(d) + __builtin_amdgcn_sqrt(__builtin_fma(d, d, h * h));
+    double w = __builtin_amdgcn_rcp(e);
+    w = __builtin_fma(__builtin_fma(-e, w, 1.0), w, w);
+    const double t = (d >= 0.0 ? h : -h) * w;
+    const double f = __builtin_fma(t, t, 1.0);              // c = f^(-1/2), f in [1, 2]: three Newton steps
+    double c = __builtin_amdgcn_rsq(f);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c = __builtin_fma(c * 0.5, __builtin_fma(-f * c, c, 1.0), c);
+    const double s = c * t;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r + 1 < R || l + 16 * r < n) {
+            up[l + 16 * r] = c * x[r] - s * y[r];
+            uq[l + 16 * r] = s * x[r] + c * y[r];
+        }
+    return double2{c, s};
+}
+
+constexpr int kJacThreads = 1024;
+constexpr int kJacPad = 1;                                  // columns n + 1 doubles apart: spreads the LDS banks
+
+template <int R>
+__device__ inline bool jacobi_sweep(double* U, int n, double2* rot, double tol) {
+    const int tid = threadIdx.x, l = tid & 15, grp = tid >> 4;
+    const int m = n + (n & 1), np = m / 2, ld = n + kJacPad;
+    bool rotated = false;
+    for (int step = 0; step < m - 1; ++step) {
+        for (int k = grp; k < np; k += kJacThreads / 16) {
+            int p = rr_player(k, step, m), q = rr_player(m - 1 - k, step, m);
+            double2 cs{1.0, 0.0};
+            if (p < n && q < n) {                           // not the idle player of an odd n
+                if (p > q) { const int t = p; p = q; q = t; }
+                cs = jacobi_pair<R>(U + p * ld, U + q * ld, n, l, tol, rotated);
+            }
+            if (l == 0) rot[(int64_t)step * np + k] = cs;
+        }
+        __syncthreads();
+    }
+    return rotated;
+}
+
+__device__ inline bool jacobi_sweep_n(double* U, int n, double2* rot, double tol) {
+    switch ((n + 15) / 16) {
+        case 1: return jacobi_sweep<1>(U, n, rot, tol);
+        case 2: return jacobi_sweep<2>(U, n, rot, tol);
+        case 3: return jacobi_sweep<3>(U, n, rot, tol);
+        case 4: return jacobi_sweep<4>(U, n, rot, tol);
+        case 5: return jacobi_sweep<5>(U, n, rot, tol);
+        case 6: return jacobi_sweep<6>(U, n, rot, tol);
+        case 7: return jacobi_sweep<7>(U, n, rot, tol);
+        case 8: return jacobi_sweep<8>(U, n, rot, tol);
+        default: return jacobi_sweep<9>(U, n, rot, tol);
+    }
+}
+
+// Row i of Q: the rotations of one sweep in order, one wave (v: its row in LDS).
+__device__ inline void jacobi_row(double* v, double* q, int n, int i, const double2* rot, bool first) {
+    const int lane = threadIdx.x & 63;
+    for (int j = lane; j < n; j += 64) v[j] = first ? (j == i ? 1.0 : 0.0) : q[(int64_t)i * n + j];
+    const int m = n + (n & 1), np = m / 2;
+    constexpr int NK = (kJacobiLds / 2 + 63) / 64;          // pairs per lane
+    double2 next[NK];
+#pragma unroll
+    for (int u = 0; u < NK; ++u) next[u] = lane + 64 * u < np ? rot[lane + 64 * u] : double2{1.0, 0.0};
+    for (int step = 0; step < m - 1; ++step) {
+        double2 cs[NK];
+#pragma unroll
+        for (int u = 0; u < NK; ++u) {
+            cs[u] = next[u];
+            if (step + 2 < m && lane + 64 * u < np) next[u] = rot[(int64_t)(step + 1) * np + lane + 64 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < NK; ++u) {
+            const int k = lane + 64 * u;
+            if (k >= np) continue;
+            int p = rr_player(k, step, m), q2 = rr_player(m - 1 - k, step, m);
+            if (p >= n || q2 >= n) continue;
+            if (p > q2) { const int t = p; p = q2; q2 = t; }
+            const double x = v[p], y = v[q2];
+            v[p] = cs[u].x * x - cs[u].y * y;
+            v[q2] = cs[u].y * x + cs[u].x * y;
+        }
+        __builtin_amdgcn_wave_barrier();                    // the wave's LDS accesses stay in step order
+    }
+    for (int j = lane; j < n; j += 64) q[(int64_t)i * n + j] = v[j];
+}
+
+// Sweep `sweep` of every unfinished factor (the first nitems workgroups; not when `last`), and the
+// previous sweep's rotations on the rows of Q (the others: rows / 16 per factor).
+__global__ __launch_bounds__(kJacThreads) void k_jacobi_round(const JacobiItem* items, JacobiState* state, int nitems,
+                                                              int sweep, int last, double tol) {
+    __shared__ double U[kJacobiLds * (kJacobiLds + kJacPad)];
+    __shared__ int s_rotated;
+    const int b = blockIdx.x, tid = threadIdx.x, now = sweep & 1;
+    if (b >= nitems) {
+        const int f = (b - nitems) % nitems, i = (b - nitems) / nitems * (kJacThreads / 64) + (tid >> 6);
+        const JacobiItem it = items[f];
+        if (i >= it.n || !(sweep == 1 || state[f].rotated[now ^ 1])) return;    // sweep 0 starts Q in any case
+        jacobi_row(U + (tid >> 6) * kJacobiLds, it.q, it.n, i, it.rot + (now ^ 1) * jacobi_rotations(it.n),
+                   sweep == 1);
+        return;
+    }
+    if (last) return;
+    JacobiState& st = state[b];
+    if (sweep > 0 && st.done) {
+        if (tid == 0) st.rotated[now] = 0;
+        return;
+    }
+    const JacobiItem it = items[b];
+    const int n = it.n, ld = n + kJacPad;
+    const double* src = sweep == 0 ? it.A : it.u;
+    if (tid == 0) s_rotated = 0;
+    for (int e = tid; e < n * n; e += kJacThreads) U[(e / n) * ld + e % n] = src[e];
+    __syncthreads();
+    if (jacobi_sweep_n(U, n, it.rot + now * jacobi_rotations(n), tol)) s_rotated = 1;
+    __syncthreads();
+    for (int e = tid; e < n * n; e += kJacThreads) it.u[e] = U[(e / n) * ld + e % n];
+    if (tid == 0) {
+        st.done = !s_rotated;
+        st.rotated[now] = s_rotated;
+    }
+}
+
+// Q^T and the eigenvalues of every factor: lam_j = v_j . u_j, one wave a column.
+__global__ __launch_bounds__(kThreads) void k_jacobi_finish(const JacobiItem* items) {
+    const JacobiItem it = items[blockIdx.y];
+    const int n = it.n, lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j >= n) return;
+    double s = 0.0;
+    for (int i = lane; i < n; i += 64) {
+        const double v = it.q[(int64_t)i * n + j];
+        it.vt[(int64_t)j * n + i] = v;
+        s = __builtin_fma(it.u[(int64_t)j * n + i], v, s);
+    }
+    s = wave_sum(s);
+    if (lane == 0) it.lam[j] = s;
+}
+
 // lam_j = v_j . u_j = v_j^T A v_j (the Rayleigh quotient of the converged column).
 __global__ __launch_bounds__(kThreads) void k_jacobi_values(const double* U, const double* V, int64_t n, double* lam) {
     __shared__ double red[4];
@@ -134,6 +319,34 @@ int32_t jacobi_eig(const double* A, int64_t n, double* V, double* lam, double* w
         if (h <= tol) break;
     }
     hipLaunchKernelGGL(k_jacobi_values, dim3((unsigned)n), dim3(kThreads), 0, s, work, V, n, lam);
+    return hipGetLastError() == hipSuccess ? COLA_OK : COLA_ERR_HIP;
+}
+
+int32_t jacobi_eig_batch(const JacobiItem* items, JacobiState* state, int nitems, int nmax, double tol,
+                         int max_sweeps, hipStream_t s) {
+    if (nitems < 1 || nitems > 65535 || nmax > kJacobiLds) return COLA_ERR_INVALID_ARG;
+    const unsigned blocks = (unsigned)nitems * (1 + (nmax + kJacThreads / 64 - 1) / (kJacThreads / 64));
+    std::vector<JacobiState> h(nitems);
+    constexpr int kAhead = 6;                               // sweeps enqueued between two looks at the state
+    for (int sweep = 0; sweep < max_sweeps;) {
+        for (int u = 0; u < kAhead && sweep < max_sweeps; ++u, ++sweep)
+            hipLaunchKernelGGL(k_jacobi_round, dim3(sweep == 0 ? (unsigned)nitems : blocks), dim3(kJacThreads), 0, s,
+                               items, state, nitems, sweep, 0, tol);
+        if (hipGetLastError() != hipSuccess) return COLA_ERR_HIP;
+        const bool end = sweep >= max_sweeps;
+        if (hipMemcpyAsync(h.data(), state, sizeof(JacobiState) * nitems, hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess)
+            return COLA_ERR_HIP;
+        bool done = true;
+        for (const JacobiState& st : h) done = done && st.done;
+        if (done || end) {                                  // the last sweep's rotations (none if all are done)
+            hipLaunchKernelGGL(k_jacobi_round, dim3(blocks), dim3(kJacThreads), 0, s, items, state, nitems, sweep, 1,
+                               tol);
+            break;
+        }
+    }
+    const dim3 rows((unsigned)((nmax + 3) / 4), (unsigned)nitems);
+    hipLaunchKernelGGL(k_jacobi_finish, rows, dim3(kThreads), 0, s, items);
     return hipGetLastError() == hipSuccess ? COLA_OK : COLA_ERR_HIP;
 }
 
