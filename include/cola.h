@@ -348,9 +348,10 @@ int32_t cola_autotune_import(cola_op_t op, const char* text);
  * Synchronises the device and drops captured chunk graphs.  Returns
  * COLA_ERR_INVALID_ARG for an unknown engine. */
 #define COLA_ENGINE_FUSED_CG 1  /* persistent CG, one cooperative launch per chunk of iterations:
-                                   one-term K1 (x) K2 (x) K3 (+ diag) with 64-wide modes, FP32
-                                   working precision, no residual history.  With check_every
-                                   = 0 every chunk of 128 iterations is enqueued up front
+                                   one-term K1 (x) K2 (x) K3 (+ diag) with modes of up to 64, FP32
+                                   working precision, no residual history, where it is the faster
+                                   one (64-wide modes; small ones; more than 4 right-hand sides).  With check_every
+                                   = 0 every chunk (128 iterations with 64-wide modes, else 32) is enqueued up front
                                    (capture-safe); a barrier time-out, which a captured launch
                                    can meet if other work shares the GPU, is then reported
                                    as COLA_ERR_HIP in every right-hand side's info          */

@@ -626,17 +626,26 @@ int32_t ensure_fused(cola_op_s* op) {
     return rc;
 }
 
-bool fused_eligible(const cola_op_s* op, const SysInfo& s, int prec, int check_every) {
-    // the persistent kernel runs its own vector update, which records no residual history
-    return op->use_fused && check_every >= 0 && op->fused_max_blocks != 0 && prec == op->prec && !op->ws.rh.data &&
-           fused_cg_supported(prec, s.Fv, s.J, s.dims);
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;                   // the null stream while another one is captured
+    }
+    return status != hipStreamCaptureStatusNone;
 }
 
-// CG iterations of a one-term three-mode FP32 operator with 64-wide modes:
+bool fused_eligible(const cola_op_s* op, const SysInfo& s, int prec, int check_every, int nrhs) {
+    // the persistent kernel runs its own vector update, which records no residual history
+    return op->use_fused && check_every >= 0 && op->fused_max_blocks != 0 && prec == op->prec && !op->ws.rh.data &&
+           fused_cg_supported(prec, s.Fv, s.J, s.dims) && fused_cg_pays(s.dims, nrhs);
+}
+
+// CG iterations of a one-term three-mode FP32 operator with modes of up to 64:
 // every chunk of check_every iterations is one cooperative launch per batch of
 // right-hand sides (then the reliable-update tail), with the host reading the
 // count of active right-hand sides one chunk behind, as in the graph path.
-// check_every == 0: every chunk (128 iterations between reliable updates) is
+// check_every == 0: every chunk (128 or 32 iterations between reliable updates) is
 // enqueued up front with no host wait, so the caller may capture the solve;
 // groups that are no longer active leave a launch at once, and a barrier
 // time-out is reported per right-hand side instead of by a host check.
@@ -644,13 +653,22 @@ int32_t run_cg_fused(cola_op_s* op, const SysInfo& s, int nrhs, float* x, float*
                      int check_every, const ReliableTail* tail, hipStream_t st) {
     Workspace& w = op->ws;
     const bool host_checks = check_every > 0;
-    const int chunk = host_checks ? std::min(check_every, max_iters) : (tail ? std::min(128, max_iters) : max_iters);
+    // between reliable updates without host checks: 128 iterations with 64-wide modes, else the 32 of run_cg
+    const bool full = s.dims[0] == 64 && s.dims[1] == 64 && s.dims[2] == 64;
+    const int chunk = host_checks ? std::min(check_every, max_iters)
+                                  : (tail ? std::min(full ? 128 : 32, max_iters) : max_iters);
     const int nchunks = (max_iters + chunk - 1) / chunk;
-    const int bpr = fused_cg_blocks_per_rhs(nrhs, op->fused_max_blocks);
+    const FusedShape shape = fused_cg_shape(s.dims, nrhs, op->fused_max_blocks);
+    const int bpr = shape.bpr;
+    if (bpr < 1) return COLA_ERR_UNSUPPORTED;
     const int per_launch = op->fused_max_blocks / bpr;
     const int64_t n = s.n;
     FusedCgArgs a{};
     a.bpr = bpr;
+    a.spq = shape.spq;
+    a.n1 = (int32_t)s.dims[0];
+    a.n2 = (int32_t)s.dims[1];
+    a.n3 = (int32_t)s.dims[2];
     a.iters = chunk;
     a.K1 = op->fac32 + s.fac_off[0];
     a.K2 = op->fac32 + s.fac_off[1];
@@ -723,7 +741,9 @@ int32_t run_cg(cola_op_s* op, const SysInfo& s, int prec, int nrhs, T* x, T* r, 
                int check_every, const ReliableTail* tail, hipStream_t st) {
     Workspace& w = op->ws;
     if constexpr (sizeof(T) == 4) {
-        if (fused_eligible(op, s, prec, check_every) && ensure_fused(op) == COLA_OK) {
+        // a first solve under the caller's capture cannot allocate: the separate kernels run it
+        if (fused_eligible(op, s, prec, check_every, nrhs) && (op->fused_slots || !capturing(st)) &&
+            ensure_fused(op) == COLA_OK) {
             const int32_t rc = run_cg_fused(op, s, nrhs, x, r, p, max_iters, check_every, tail, st);
             if (rc != COLA_ERR_UNSUPPORTED) return rc;
         }
@@ -1446,7 +1466,7 @@ int32_t cola_op_create(const cola_system_desc* systems, int32_t nsys, int32_t pr
     // working copies
     if (prec != COLA_PREC_FP64) {
         rc = dev_alloc(op, (void**)&op->fac32, sizeof(float) * (fac + 32));
-        if (rc == COLA_OK && dg > 0) rc = dev_alloc(op, (void**)&op->diag32, sizeof(float) * dg);
+        if (rc == COLA_OK && dg > 0) rc = dev_alloc(op, (void**)&op->diag32, sizeof(float) * (dg + 64));
         if (rc == COLA_OK && (prec == COLA_PREC_BF16 || prec == COLA_PREC_BF16X3)) {
             op->nsplit = (prec == COLA_PREC_BF16) ? 1 : 3;
             rc = dev_alloc(op, (void**)&op->facbf, sizeof(__bf16) * fac * op->nsplit);

@@ -1,4 +1,4 @@
-// Persistent fused CG for one-term three-mode FP32 operators with 64-wide modes.
+// Persistent fused CG for one-term three-mode FP32 operators with modes of up to 64.
 //
 // The separate-kernel path runs three launches per CG iteration (modes 2 and 3
 // of the Kronecker MVM per slab, mode 1 with the direction update, the vector
@@ -7,10 +7,10 @@
 // only ever exchange data with each other, so they meet at group barriers
 // rather than grid-wide ones; each iteration has three phases:
 //
-//   A  per slab X[i1] (64 x 64): p = r + beta p (written back to p), then
+//   A  per slab X[i1] (n2 x n3, at most 64 x 64): p = r + beta p (written back to p), then
 //      T[i1] = K2 P[i1] K3^T  (modes 2 and 3, the per-mode evaluation behind
 //      the Kronecker MVM cost of Table 2);
-//   B  per column strip (64 rows i1 x 64 columns (i2, i3)): q = K1 T +
+//   B  per column strip (all rows i1 x 64 columns (i2, i3)): q = K1 T +
 //      (sigma2 + d) p and the partial p.q; q stays in registers;
 //   C  after the group sum of p.q gives alpha: r -= alpha q and the partial
 //      r.r, whose group sum gives the convergence test and beta.
@@ -37,32 +37,49 @@ namespace {
 
 constexpr int D = 64;                      // mode size
 constexpr int PD = D + 4;                  // LDS row pitch (floats)
-constexpr int SL = D * D;                  // elements per slab and per strip
-constexpr int NV = D * D * D;              // unknowns per right-hand side
 constexpr int kFT = 1024;                  // threads per block: 4 quads of 4 waves
 constexpr int kSC1 = 16;                   // cache-policy operand: agent-coherent access
 constexpr uint32_t kSpinLimit = 1u << 22;  // barrier polls before a time-out (seconds)
 
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
-__device__ inline __amdgpu_buffer_rsrc_t vec_rsrc(const float* base) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, NV * 4, 0x00020000);
+// n elements and the 256 bytes after them: where modes are narrower than 64, loads of a tile's edge
+// run past the end by less than that (the CG vectors have room for twice their n >= 64 elements, the
+// diagonal is padded), and what lies outside the tile is replaced by zeros.
+__device__ inline __amdgpu_buffer_rsrc_t vec_rsrc(const float* base, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, n * 4 + 256, 0x00020000);
 }
 // Element offsets split into a per-lane part and a wave-uniform part (kept in
 // a scalar register), so the addresses of an unrolled loop cost no registers.
 __device__ inline floatx4 ldc(__amdgpu_buffer_rsrc_t rs, int lane_e, int uni_e) {
     return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_e * 4, uni_e * 4, kSC1));
 }
-__device__ inline void stc(__amdgpu_buffer_rsrc_t rs, int lane_e, int uni_e, floatx4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), rs, lane_e * 4, uni_e * 4, kSC1);
-}
 // The same through the ordinary cache path, for data only this block touches
 // (x) or nobody writes (the diagonal); a resource of zero records reads zeros.
 __device__ inline floatx4 ldn(__amdgpu_buffer_rsrc_t rs, int lane_e, int uni_e) {
     return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_e * 4, uni_e * 4, 0));
 }
-__device__ inline void stn(__amdgpu_buffer_rsrc_t rs, int lane_e, int uni_e, floatx4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), rs, lane_e * 4, uni_e * 4, 0);
+// The first `valid` elements of v, zeros after them.
+template <bool FULL>
+__device__ inline floatx4 first_of(floatx4 v, int valid) {
+    if constexpr (!FULL) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = c < valid ? v[c] : 0.f;
+    }
+    return v;
+}
+// Store the first `valid` elements (POLICY: the cache policy of stc or stn).
+template <bool FULL, int POLICY>
+__device__ inline void store_of(__amdgpu_buffer_rsrc_t rs, int lane_e, int uni_e, floatx4 v, int valid) {
+    if (FULL || valid >= 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), rs, lane_e * 4, uni_e * 4, POLICY);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (c < valid)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, (float)v[c]), rs,
+                                                      (lane_e + c) * 4, uni_e * 4, POLICY);
+    }
 }
 __device__ inline floatx4 mma(float a, float b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -151,8 +168,10 @@ struct FState {
     int pending;                  // x += alpha p of the last finished iteration not applied yet
 };
 
-// SPQ: slabs (phase A) and strips (phases B, C) per quad; a block owns 4 SPQ of each.
-template <int SPQ>
+// SPQ: slabs (phase A) and strips (phases B, C) per quad; a block owns 4 SPQ of each.  FULL: every
+// mode 64 wide; otherwise any sizes up to that, with tiles and vectors cut at the edges (rows of
+// n3 elements need not be 16-byte aligned).
+template <int SPQ, bool FULL>
 __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
     __shared__ __attribute__((aligned(16))) float K1s[D * PD];
     __shared__ __attribute__((aligned(16))) float K2s[D * PD];
@@ -183,21 +202,23 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
         fs.pending = 0;
     }
 
-    const auto rsX = vec_rsrc(a.x + (int64_t)grp * NV);
+    const int n1 = FULL ? D : a.n1, n2 = FULL ? D : a.n2, n3 = FULL ? D : a.n3;
+    const int n23 = n2 * n3, nv = n1 * n23;          // elements of a slab, unknowns per right-hand side
+    const auto rsX = vec_rsrc(a.x + (int64_t)grp * nv, nv);
     const auto rsD = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dvec), (short)0,
-                                                       a.dvec ? NV * 4 : 0, 0x00020000);
-    const auto rsR = vec_rsrc(a.r + (int64_t)grp * NV);
-    const auto rsP = vec_rsrc(a.p + (int64_t)grp * NV);
-    const auto rsT = vec_rsrc(a.T + (int64_t)grp * NV);
+                                                       a.dvec ? nv * 4 + 256 : 0, 0x00020000);
+    const auto rsR = vec_rsrc(a.r + (int64_t)grp * nv, nv);
+    const auto rsP = vec_rsrc(a.p + (int64_t)grp * nv, nv);
+    const auto rsT = vec_rsrc(a.T + (int64_t)grp * nv, nv);
     const float s2 = (float)a.sigma2;
     double* gslots = a.slots + (int64_t)grp * 3 * a.bpr;
     uint32_t k = 0;                                  // barriers passed in this launch
 
     for (int e = tid; e < D * D; e += kFT) {
         const int rr = e / D, c = e % D;
-        K1s[rr * PD + c] = a.K1[e];
-        K2s[rr * PD + c] = a.K2[e];
-        K3s[rr * PD + c] = a.K3[e];
+        K1s[rr * PD + c] = rr < n1 && c < n1 ? a.K1[rr * n1 + c] : 0.f;
+        K2s[rr * PD + c] = rr < n2 && c < n2 ? a.K2[rr * n2 + c] : 0.f;
+        K3s[rr * PD + c] = rr < n3 && c < n3 ? a.K3[rr * n3 + c] : 0.f;
     }
 
     const int u0 = (rank * 4 + quad) * SPQ;          // this quad's first slab / strip
@@ -205,23 +226,39 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
     // phase A lane roles: row 16 qw + lr of the slab; the first product's k index
     // at step s = 4 u + c is column 16 u + 4 lq + c (4 consecutive columns per lane)
     const int arow = 16 * qw + lr;
-    const int alane = arow * D + 4 * lq;            // + 16 u: this lane's elements of a slab
+    auto at_most = [](int i, int last) { return FULL ? i : (i < last ? i : last); };   // in bounds
+    const int alane = at_most(arow, n2 - 1) * n3 + 4 * lq;   // + 16 u: this lane's elements of a slab
+    auto slab_at = [&](int sl) { return at_most(sl, n1 - 1) * n23; };
+    const int last_strip = ((n23 - 1) / D) * D;
+    const bool arow_in = FULL || arow < n2;
+    auto avalid = [&](int sl, int u) { return FULL ? 4 : (sl < n1 && arow_in ? n3 - 16 * u - 4 * lq : 0); };
     // T write-out: float4 number qt + 256 q of a slab is row qt / 16 + 16 q, column 4 (qt % 16)
-    const int tlane = (qt >> 4) * D + 4 * (qt & 15);
+    const int tlane = (qt >> 4) * n3 + 4 * (qt & 15);
     const int tlds = (qt >> 4) * PD + 4 * (qt & 15);
     // phase B staging of a T strip: row qt / 4, columns 16 u + 4 (qt % 4) + c
     const int brow = qt >> 2, bsub = qt & 3;
-    const int blane = brow * (D * D) + 4 * bsub;    // + 16 u (+ strip column c0)
+    const int blane = at_most(brow, n1 - 1) * n23 + 4 * bsub;   // + 16 u (+ strip column c0)
     // phases B, C output roles: the transposed product Q^T = T^T K1^T puts 4 consecutive
     // columns of one output row in each lane; tile (ti, tj) of wave (wm, wn) holds row
     // 32 wn + 16 tj + lr, columns c0 + 32 wm + 16 ti + 4 lq + v
-    const int olane = (32 * wn + lr) * (D * D) + 32 * wm + 4 * lq;   // + 16 ti (+ c0 + 16 D^2 tj)
+    // (lane part + 16 ti, and with 64-wide modes a uniform part 16 n23 tj)
+    int olane[FULL ? 1 : 2];
+#pragma unroll
+    for (int tj = 0; tj < (FULL ? 1 : 2); ++tj)
+        olane[tj] = at_most(32 * wn + 16 * tj + lr, n1 - 1) * n23 + 32 * wm + 4 * lq;
+    auto olane_of = [&](int tj) { return olane[FULL ? 0 : tj]; };
+    auto strip_at = [&](int c0, int tj) { return FULL ? c0 + 16 * n23 * tj : at_most(c0, last_strip); };
+    auto ovalid = [&](int c0, int ti, int tj) {
+        return FULL ? 4 : (32 * wn + 16 * tj + lr < n1 ? n23 - c0 - 32 * wm - 16 * ti - 4 * lq : 0);
+    };
+    // tiles and k extents in use (wave-uniform)
+    const int ku3 = FULL ? 4 : (n3 + 15) / 16, kk2 = FULL ? D : (n2 + 3) & ~3, kk1 = FULL ? D : (n1 + 3) & ~3;
 
     float pv[16], rv[16];                            // phase A operands of the current slab
     auto load_p = [&](int sl) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const floatx4 pp = ldc(rsP, alane + 16 * u, sl * SL);
+            const floatx4 pp = first_of<FULL>(ldc(rsP, alane + 16 * u, slab_at(sl)), avalid(sl, u));
 #pragma unroll
             for (int c = 0; c < 4; ++c) pv[4 * u + c] = pp[c];
         }
@@ -229,7 +266,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
     auto load_r = [&](int sl) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const floatx4 r4 = ldc(rsR, alane + 16 * u, sl * SL);
+            const floatx4 r4 = first_of<FULL>(ldc(rsR, alane + 16 * u, slab_at(sl)), avalid(sl, u));
 #pragma unroll
             for (int c = 0; c < 4; ++c) rv[4 * u + c] = r4[c];
         }
@@ -251,18 +288,21 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
                 const int sl = u0 + s;
                 floatx4 xv[4];                         // x arrives during the first product
 #pragma unroll
-                for (int u = 0; u < 4; ++u) xv[u] = ldn(rsX, alane + 16 * u, sl * SL);
+                for (int u = 0; u < 4; ++u) xv[u] = ldn(rsX, alane + 16 * u, slab_at(sl));
                 float av[16];
 #pragma unroll
                 for (int q = 0; q < 16; ++q) av[q] = pnew_of(rv[q], pv[q], beta);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    stc(rsP, alane + 16 * u, sl * SL, floatx4{av[4 * u], av[4 * u + 1], av[4 * u + 2], av[4 * u + 3]});
+                    store_of<FULL, kSC1>(rsP, alane + 16 * u, sl * n23,
+                                         floatx4{av[4 * u], av[4 * u + 1], av[4 * u + 2], av[4 * u + 3]},
+                                         avalid(sl, u));
                 floatx4 acc1[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc1[j] = floatx4{0, 0, 0, 0};
 #pragma unroll
                 for (int st = 0; st < 16; ++st) {
+                    if (!FULL && (st >> 2) >= ku3) break;
                     const int kcol = 16 * (st >> 2) + 4 * lq + (st & 3);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) acc1[j] = mma(av[st], K3s[(16 * j + lr) * PD + kcol], acc1[j]);
@@ -272,7 +312,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
                     for (int u = 0; u < 4; ++u) {
 #pragma unroll
                         for (int c = 0; c < 4; ++c) xv[u][c] = __builtin_fmaf(aprev, pv[4 * u + c], xv[u][c]);
-                        stn(rsX, alane + 16 * u, sl * SL, xv[u]);
+                        store_of<FULL, 0>(rsX, alane + 16 * u, sl * n23, xv[u], avalid(sl, u));
                     }
                 }
                 if (s + 1 < SPQ) {                     // next slab in flight during the second product
@@ -290,7 +330,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
 #pragma unroll
                     for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0, 0, 0, 0};
 #pragma unroll 4
-                for (int k = 0; k < D; k += 4) {
+                for (int k = 0; k < kk2; k += 4) {
                     float a2[2], b2[2];
 #pragma unroll
                     for (int i = 0; i < 2; ++i) a2[i] = K2s[(32 * wm + 16 * i + lr) * PD + k + lq];
@@ -313,7 +353,8 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const floatx4 t4 = *(const floatx4*)(Wt + tlds + 16 * PD * q);
-                    stc(rsT, tlane, sl * SL + 16 * D * q, t4);
+                    const bool in = FULL || (sl < n1 && (qt >> 4) + 16 * q < n2);
+                    store_of<FULL, kSC1>(rsT, tlane, sl * n23 + 16 * n3 * q, t4, in ? n3 - 4 * (qt & 15) : 0);
                 }
                 __syncthreads();                               // T read out before the next slab
             }
@@ -334,11 +375,14 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
             auto load_strip = [&](int s, floatx4* tv_, floatx4 (*pb_)[2]) {
                 const int c0 = (u0 + s) * D;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) tv_[u] = ldc(rsT, blane + 16 * u, c0);
+                for (int u = 0; u < 4; ++u)
+                    tv_[u] = first_of<FULL>(ldc(rsT, blane + 16 * u, strip_at(c0, 0)),
+                                            FULL || brow < n1 ? n23 - c0 - 16 * u - 4 * bsub : 0);
 #pragma unroll
                 for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-                    for (int tj = 0; tj < 2; ++tj) pb_[ti][tj] = ldc(rsP, olane + 16 * ti, c0 + 16 * SL * tj);
+                    for (int tj = 0; tj < 2; ++tj)
+                        pb_[ti][tj] = first_of<FULL>(ldc(rsP, olane_of(tj) + 16 * ti, strip_at(c0, tj)), ovalid(c0, ti, tj));
             };
             load_strip(0, tv, pb);
 #pragma unroll
@@ -355,7 +399,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
 #pragma unroll
                     for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0, 0, 0, 0};
 #pragma unroll 4
-                for (int k = 0; k < D; k += 4) {
+                for (int k = 0; k < kk1; k += 4) {
                     float ta[2], kb[2];
 #pragma unroll
                     for (int ti = 0; ti < 2; ++ti) ta[ti] = Wt[(k + lq) * PD + 32 * wm + 16 * ti + lr];
@@ -370,7 +414,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
                 for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
                     for (int tj = 0; tj < 2; ++tj) {
-                        const floatx4 d4 = ldn(rsD, olane + 16 * ti, c0 + 16 * SL * tj);
+                        const floatx4 d4 = first_of<FULL>(ldn(rsD, olane_of(tj) + 16 * ti, strip_at(c0, tj)), ovalid(c0, ti, tj));
                         floatx4 q;
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
@@ -401,7 +445,8 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
             for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
                 for (int tj = 0; tj < 2; ++tj)
-                    rh[s][ti][tj] = ldc(rsR, olane + 16 * ti, (u0 + s) * D + 16 * SL * tj);
+                    rh[s][ti][tj] = first_of<FULL>(ldc(rsR, olane_of(tj) + 16 * ti, strip_at((u0 + s) * D, tj)),
+                                                   ovalid((u0 + s) * D, ti, tj));
         if (!group_gather(gslots, a.bpr, rank, k++, a.err, &s_tot, &s_ok)) return;
         if (tid == 0) {
             const double pq = s_tot;
@@ -432,7 +477,8 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
                         r4[v] = __builtin_fmaf(-af, qh[s][ti][tj][v], r4[v]);
                         rr2 += (double)r4[v] * (double)r4[v];
                     }
-                    stc(rsR, olane + 16 * ti, (u0 + s) * D + 16 * SL * tj, r4);
+                    store_of<FULL, kSC1>(rsR, olane_of(tj) + 16 * ti, strip_at((u0 + s) * D, tj), r4,
+                                         ovalid((u0 + s) * D, ti, tj));
                 }
         const double rr_blk = block_sum16(rr2, red);
         fence_stores();                                        // r visible to the group
@@ -479,12 +525,12 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
         for (int s = 0; s < SPQ; ++s)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int sb = (u0 + s) * SL;
+                const int sb = slab_at(u0 + s);
                 const floatx4 p4 = ldc(rsP, alane + 16 * u, sb);
                 floatx4 x4 = ldn(rsX, alane + 16 * u, sb);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) x4[c] = __builtin_fmaf(af, p4[c], x4[c]);
-                stn(rsX, alane + 16 * u, sb, x4);
+                store_of<FULL, 0>(rsX, alane + 16 * u, sb, x4, avalid(u0 + s, u));
             }
     }
     if (rank == 0 && tid == 0) {
@@ -501,26 +547,59 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
 }  // namespace
 
 bool fused_cg_supported(int prec, int Fv, int J, const int64_t* dims) {
-    return prec == COLA_PREC_FP32 && Fv == 3 && J == 1 && dims[0] == D && dims[1] == D && dims[2] == D;
+    return prec == COLA_PREC_FP32 && Fv == 3 && J == 1 && dims[0] <= D && dims[1] <= D && dims[2] <= D &&
+           dims[0] * dims[1] * dims[2] >= 64;
 }
 
+namespace {
+const void* const kFusedKernels[2][2] = {
+    {(const void*)k_fused_cg<1, false>, (const void*)k_fused_cg<1, true>},
+    {(const void*)k_fused_cg<2, false>, (const void*)k_fused_cg<2, true>},
+};
+}  // namespace
+
 int fused_cg_max_blocks() {
-    int dev = 0, coop = 0, cus = 0, per_cu = 0;
+    int dev = 0, coop = 0, cus = 0, least = 1 << 30;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    int p2 = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused_cg<2>, kFT, 0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&p2, k_fused_cg<1>, kFT, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        return 0;
-    }
-    return std::min(per_cu, p2) * cus;
+    for (const auto& row : kFusedKernels)
+        for (const void* fn : row) {
+            int per_cu = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kFT, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                return 0;
+            }
+            least = std::min(least, per_cu);
+        }
+    return least * cus;
 }
 
-int fused_cg_blocks_per_rhs(int nrhs, int max_blocks) {
-    if (max_blocks < 8) return 0;
-    return (nrhs * 16 <= max_blocks) ? 16 : 8;
+namespace {
+// Slabs (n1) and strips (n2 n3 / 64) of a right-hand side.
+int64_t units_of(const int64_t* dims) { return std::max(dims[0], (dims[1] * dims[2] + D - 1) / D); }
+}  // namespace
+
+// An iteration is three group barriers, whose cost grows with the group, and hardly depends on the
+// number of right-hand sides until the chip is full; three kernels cost about 23 us an iteration
+// and then by volume.  Measured, fused against separate kernels, us an iteration: 16^3, groups of 4:
+// 18 / 23 at 1 right-hand side, 19 / 27 at 32; 32^3, groups of 8: 22.5 / 23 at 1, 23 / 30 at 16;
+// 50^3, groups of 16: 32.5 / 28 at 1, 32 / 31 at 4, 36.5 / 58 at 16; 60 x 20 x 20, groups of 16:
+// 24.5 / 24 at 4, 26 / 35 at 16; 48 x 40 x 56 at 16: 31 / 54.
+bool fused_cg_pays(const int64_t* dims, int nrhs) {
+    const bool full = dims[0] == D && dims[1] == D && dims[2] == D;
+    return full || units_of(dims) <= 32 || nrhs > 4;
+}
+
+// The slabs (n1) and strips (n2 n3 / 64) of a right-hand side, one to a quad if all right-hand sides
+// then fit the chip at once, else two; 4 quads to a block.
+FusedShape fused_cg_shape(const int64_t* dims, int nrhs, int max_blocks) {
+    if (max_blocks < 8) return FusedShape{0, 0};
+    const int64_t units = units_of(dims);
+    int bpr = 4;
+    while (4 * bpr < units) bpr *= 2;                      // 4, 8 or 16 blocks
+    if ((int64_t)nrhs * bpr <= max_blocks || bpr == 4) return FusedShape{bpr, 1};
+    return FusedShape{bpr / 2, 2};
 }
 
 namespace {
@@ -539,11 +618,14 @@ hipError_t fused_cg_report_timeout(const uint32_t* err, CgState* cg, int nrhs, h
 }
 
 hipError_t launch_fused_cg(const FusedCgArgs& a, hipStream_t s) {
-    if (a.nrhs < 1 || (a.bpr != 8 && a.bpr != 16)) return hipErrorInvalidValue;
+    if (a.nrhs < 1 || a.bpr < 4 || a.bpr > 16 || a.spq < 1 || a.spq > 2 || a.n1 < 1 || a.n2 < 1 || a.n3 < 1 ||
+        a.n1 > D || a.n2 > D || a.n3 > D || 4 * a.bpr * a.spq < a.n1 || 4 * a.bpr * a.spq * D < a.n2 * a.n3)
+        return hipErrorInvalidValue;
     FusedCgArgs args = a;
     void* kargs[] = {&args};
-    const void* fn = a.bpr == 8 ? (const void*)k_fused_cg<2> : (const void*)k_fused_cg<1>;
-    return hipLaunchCooperativeKernel(fn, dim3((unsigned)(a.nrhs * a.bpr)), dim3(kFT), kargs, 0, s);
+    const bool full = a.n1 == D && a.n2 == D && a.n3 == D;
+    return hipLaunchCooperativeKernel(kFusedKernels[a.spq - 1][full ? 1 : 0], dim3((unsigned)(a.nrhs * a.bpr)),
+                                      dim3(kFT), kargs, 0, s);
 }
 
 }  // namespace cola
