@@ -3,13 +3,24 @@
 // CoLA solves blocks of right-hand sides together and stops when all have
 // converged (App. D.5); here the block is a batch of independent systems
 // K1 (x) K2 + diag(d) + sigma2 I of uneven sizes (mode sizes up to 128).
-// Each (system, RHS) item is owned by one workgroup (16 waves) for as long as it
-// iterates: its direction P and the intermediate T = P K2^T stay in LDS,
-// x and r stay in registers laid out like the MFMA output of Q = K1 T, and
-// the factors stream through LDS in 32-column chunks.  Workgroups pull items
-// from an atomic queue ordered largest-first, so uneven iteration counts
-// balance across the chip, and every workgroup leaves once the queue is
-// empty.  An item leaves the kernel when its FP32 residual has dropped by
+// Each (system, RHS) item is owned by one workgroup of eight waves for as long
+// as it iterates.  The batch ends with its longest solves, one CU each, so what
+// counts is the time of an iteration of a large system, which is bound by its
+// FP32 MFMAs (13.7 us at 128 x 128 on one CU):
+//   - x, r and p stay in registers, in the layout of the second product's output;
+//     P and T = P K2^T pass through LDS, and both products are formed so that
+//     every LDS access moves four consecutive elements of k (T is written
+//     transposed straight from the accumulators, Q comes out transposed);
+//   - the factors are read as fragments from L2, a step of 16 k ahead, so no
+//     barrier separates slices: four barriers an iteration (two for the exchange
+//     of P and T, one for each dot product);
+//   - 16 x 16 tiles, dealt to the SIMDs along the mode that balances them.
+// 128 uneven systems (modes 16 to 128, up to 670 iterations), launch of one round:
+// 2.4 ms with the factors staged through LDS in 32-column chunks (two barriers a
+// chunk, x in memory, 36 us an iteration at 128 x 128), see k_resident_cg for now.
+// Workgroups pull items from an atomic queue ordered largest-first, so uneven
+// iteration counts balance across the chip, and every workgroup leaves once the
+// queue is empty.  An item leaves the kernel when its FP32 residual has dropped by
 // delta (or converged): the FP64 residual kernel then folds x into the FP64
 // solution, forms b - A x with the FP64 factors and replaces r, and the next
 // round resumes the same CG (reliable updates).
@@ -17,24 +28,23 @@
 
 namespace cola {
 
-constexpr int kResThreads = 1024;                // 16 waves per item
-constexpr int RPS = kResMax + 4;                 // LDS row stride of P and T (floats)
-constexpr int KC = 32;                           // factor columns staged per chunk
-constexpr int FPS = KC + 4;                      // row stride of a factor chunk
+constexpr int kResThreads = 512;                 // 8 waves per item
 constexpr int kResWaves = kResThreads / 64;
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+constexpr int RPS = kResMax + 4;                 // LDS row stride of P and T^T (floats): conflict-free 16-byte accesses
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// Sum over the 16 waves of an item's workgroup with a single barrier.  A
-// caller that sums again must use another slot array (or pass a barrier)
-// before it writes these slots again: other waves may still be reading them.
-__device__ inline double block_sum16(double v, double* smem) {
+// Sum over the WAVES waves of a workgroup with a single barrier.  A caller
+// that sums again must use another slot array (or pass a barrier) before it
+// writes these slots again: other waves may still be reading them.
+template <int WAVES>
+__device__ inline double block_sum_once(double v, double* smem) {
     v = wave_sum(v);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) smem[wave] = v;
     __syncthreads();
     double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < kResThreads / 64; ++i) s += smem[i];
+    for (int i = 0; i < WAVES; ++i) s += smem[i];
     return s;
 }
 
@@ -87,218 +97,255 @@ __global__ __launch_bounds__(kThreads) void k_resident_prepare(ResArgs a, double
     }
 }
 
-__global__ __launch_bounds__(kResThreads) void k_resident_cg(ResArgs a) {
-    __shared__ __attribute__((aligned(16))) float Ps[kResMax * RPS];   // direction p
-    __shared__ __attribute__((aligned(16))) float Ts[kResMax * RPS];   // T = P K2^T, then Q = K1 T
-    __shared__ __attribute__((aligned(16))) float Fc[kResMax * FPS];   // factor chunk
+__device__ inline floatx4 mma4(const floatx4& a, const floatx4& b, floatx4 c) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[k], c, 0, 0, 0);
+    return c;
+}
+
+// Fragments of the 16 factor rows of N tiles: lane l holds row l % 16, elements k0 + 4 (l / 16) .. + 3
+// (the factor buffer is padded past its last row; elements beyond the row are zeroed by `cut`).
+template <int N>
+struct FactorRows {
+    const float* row[N];
+    int nk, kl;                                             // mode size, this lane's first k of a step
+    floatx4 v[N];
+    __device__ void start(const float* K, int n, int first_tile, int tile_step) {
+        const int lane = threadIdx.x & 63;
+        nk = n;
+        kl = 4 * (lane >> 4);
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            int r = 16 * (first_tile + tile_step * t) + (lane & 15);
+            if (r >= n) r = n - 1;                          // its outputs are masked
+            row[t] = K + r * n + kl;
+        }
+    }
+    __device__ void load(int k0) {
+#pragma unroll
+        for (int t = 0; t < N; ++t) v[t] = *(const floatx4u*)(row[t] + k0);
+    }
+    __device__ void cut(int k0) {
+        if (k0 + 16 <= nk) return;
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[t][c] = k0 + kl + c < nk ? v[t][c] : 0.f;
+    }
+};
+
+// The iterations of one item.  This wave owns the 16 x 16 tiles (wi + GI a, wj + GJ b), a < WI,
+// b < WJ; its lane holds the elements i = 16 (wi + GI a) + lane % 16, j = 16 (wj + GJ b) + 4 (lane / 16) + v.
+template <int WI, int WJ>
+__device__ inline void resident_item(const ResArgs& a, int item, float* Ps, float* Ts, double* red_pq,
+                                     double* red_rr) {
+    constexpr int GI = 8 / WI, GJ = 8 / WJ;                 // 8 x 8 tiles at most: 8 waves
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    // wave % 4 is the SIMD: it goes along the mode with four wave columns
+    const int wi = GI == 4 ? wave & 3 : wave >> 2, wj = GJ == 4 ? wave & 3 : wave >> 2;
+    CgState* stp = &a.st[item];
+    const ResSys sy = a.sys[item / a.nrhs];
+    const int rhs = item % a.nrhs;
+    const int n1 = sy.n1, n2 = sy.n2;
+    const int t1 = (n1 + 15) / 16, t2 = (n2 + 15) / 16;     // tiles, and k steps of 16
+    const int na = (t1 - wi + GI - 1) / GI, nb = (t2 - wj + GJ - 1) / GJ;    // this wave's
+    const int64_t base = (int64_t)a.nrhs * sy.vec_off + (int64_t)rhs * sy.n;
+    const float* dgv = sy.diag_off >= 0 ? a.diag32 + sy.diag_off : nullptr;
+    const float s2 = (float)sy.sigma2;
+    FactorRows<WJ> k2;
+    FactorRows<WI> k1;
+    k2.start(a.fac32 + sy.k2_off, n2, wj, GJ);
+    k1.start(a.fac32 + sy.k1_off, n1, wi, GI);
+    auto row_of = [&](int ta) { return 16 * (wi + GI * ta) + lr; };
+    auto col_of = [&](int tb) { return 16 * (wj + GJ * tb) + 4 * lq; };
+    auto in = [&](int ta, int tb, int v) { return row_of(ta) < n1 && col_of(tb) + v < n2; };
+
+    // scalars (read by every thread; only thread 0 writes them back)
+    double rho = stp->rho, beta = stp->beta;
+    const double tol2 = stp->tol2, delta = stp->delta, rmax = stp->rmax;
+    int iters = stp->iters;
+    const int max_iters = stp->max_iters;
+    int status = stp->status, active = 1, need_update = 0;
+
+    floatx4 x[WI][WJ], r[WI][WJ], p[WI][WJ];
+#pragma unroll
+    for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < WJ; ++tb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool ok = in(ta, tb, v);
+                const int64_t e = base + (ok ? (int64_t)row_of(ta) * n2 + col_of(tb) + v : 0);
+                x[ta][tb][v] = ok ? a.x[e] : 0.f;
+                r[ta][tb][v] = ok ? a.r[e] : 0.f;
+                p[ta][tb][v] = ok ? a.p[e] : 0.f;
+            }
+
+    for (;;) {
+        k2.load(0);
+        const float bf = (float)beta;
+#pragma unroll
+        for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) p[ta][tb][v] = __builtin_fmaf(bf, p[ta][tb][v], r[ta][tb][v]);
+                if (ta < na && tb < nb) *(floatx4*)(Ps + row_of(ta) * RPS + col_of(tb)) = p[ta][tb];
+            }
+        __syncthreads();                                    // P complete
+        floatx4 acc[WI][WJ];
+#pragma unroll
+        for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb) acc[ta][tb] = floatx4{0, 0, 0, 0};
+        // T = P K2^T (A: rows of P, B: rows of K2)
+        for (int u = 0; u < t2; ++u) {
+            FactorRows<WJ> now = k2;
+            now.cut(16 * u);
+            k2.load(u + 1 < t2 ? 16 * (u + 1) : 0);         // a step ahead
+            floatx4 pa[WI];
+#pragma unroll
+            for (int ta = 0; ta < WI; ++ta) pa[ta] = *(const floatx4*)(Ps + row_of(ta) * RPS + 16 * u + 4 * lq);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < WJ; ++tb)
+                    if (ta < na && tb < nb) acc[ta][tb] = mma4(pa[ta], now.v[tb], acc[ta][tb]);
+        }
+        k1.load(0);
+        // accumulator element v of a lane: row 16 (wi + GI a) + 4 lq + v, column 16 (wj + GJ b) + lr
+#pragma unroll
+        for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb)
+                if (ta < na && tb < nb)
+                    *(floatx4*)(Ts + (16 * (wj + GJ * tb) + lr) * RPS + 16 * (wi + GI * ta) + 4 * lq) = acc[ta][tb];
+        __syncthreads();                                    // T^T complete
+#pragma unroll
+        for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb) acc[ta][tb] = floatx4{0, 0, 0, 0};
+        // Q^T = T^T K1^T (A: rows of T^T, B: rows of K1)
+        for (int u = 0; u < t1; ++u) {
+            FactorRows<WI> now = k1;
+            now.cut(16 * u);
+            k1.load(u + 1 < t1 ? 16 * (u + 1) : 0);
+            floatx4 tt[WJ];
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb)
+                tt[tb] = *(const floatx4*)(Ts + (16 * (wj + GJ * tb) + lr) * RPS + 16 * u + 4 * lq);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < WJ; ++tb)
+                    if (ta < na && tb < nb) acc[ta][tb] = mma4(tt[tb], now.v[ta], acc[ta][tb]);
+        }
+        // q = K1 T + (sigma2 + d) p;  mu = p.q
+        double mu_l = 0.0;
+#pragma unroll
+        for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const bool ok = in(ta, tb, v);
+                    const float d = dgv && ok ? dgv[row_of(ta) * n2 + col_of(tb) + v] : 0.f;
+                    const float pe = p[ta][tb][v];
+                    const float qv = ok ? acc[ta][tb][v] + (s2 + d) * pe : 0.f;
+                    acc[ta][tb][v] = qv;
+                    mu_l += (double)pe * (double)qv;
+                }
+        const double mu = block_sum_once<kResWaves>(mu_l, red_pq);
+        if (!(mu > 0.0) || !finite_d(mu)) {
+            status = finite_d(mu) ? COLA_ERR_NOT_SPD : COLA_ERR_NONFINITE;
+            active = 0;
+            break;
+        }
+        const float af = (float)(rho / mu);
+        double rho_l = 0.0;
+#pragma unroll
+        for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < WJ; ++tb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    x[ta][tb][v] = __builtin_fmaf(af, p[ta][tb][v], x[ta][tb][v]);
+                    r[ta][tb][v] = __builtin_fmaf(-af, acc[ta][tb][v], r[ta][tb][v]);
+                    rho_l += (double)r[ta][tb][v] * (double)r[ta][tb][v];
+                }
+        const double rn = block_sum_once<kResWaves>(rho_l, red_rr);
+        ++iters;
+        bool stop = false;
+        if (!finite_d(rn)) {
+            status = COLA_ERR_NONFINITE;
+            active = 0;
+            stop = true;
+        } else if (rn <= tol2) {                            // pause; the FP64 residual decides
+            need_update = 1;
+            active = 0;
+            stop = true;
+        } else if (iters >= max_iters) {
+            status = COLA_NOT_CONVERGED;
+            active = 0;
+            stop = true;
+        } else if (rn < delta * delta * rmax * rmax) {
+            need_update = 1;
+            stop = true;
+        }
+        beta = rn / rho;
+        rho = rn;
+        if (stop) break;
+    }
+    // write the state back
+#pragma unroll
+    for (int ta = 0; ta < WI; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < WJ; ++tb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (in(ta, tb, v)) {
+                    const int64_t e = base + (int64_t)row_of(ta) * n2 + col_of(tb) + v;
+                    a.x[e] = x[ta][tb][v];
+                    a.r[e] = r[ta][tb][v];
+                    a.p[e] = p[ta][tb][v];
+                }
+    if (tid == 0) {
+        stp->rho = rho;
+        stp->beta = beta;
+        stp->iters = iters;
+        stp->status = status;
+        stp->need_update = need_update;
+        if (!active) {
+            stp->active = 0;
+            atomicSub(&a.cnt->num_active, 1);
+        }
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kResThreads, 2) void k_resident_cg(ResArgs a) {
+    __shared__ __attribute__((aligned(16))) float Ps[kResMax * RPS];   // direction P
+    __shared__ __attribute__((aligned(16))) float Ts[kResMax * RPS];   // (P K2^T)^T
     __shared__ double red_pq[kResWaves];       // slots of the p.q sums
     __shared__ double red_rr[kResWaves];       // slots of the r.r sums (every other barrier of the
                                                // iteration lies between one sum's reads and its next write)
     __shared__ int s_item;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lq = lane >> 4;
-    // element ownership for the vector updates: 16 consecutive columns of one row
-    const int orow = tid >> 3, ocol = (tid & 7) * 16;
-
     for (;;) {
-        if (tid == 0) s_item = (int)atomicAdd(a.queue, 1u);
+        if (threadIdx.x == 0) s_item = (int)atomicAdd(a.queue, 1u);
         __syncthreads();
         const int q = s_item;
         __syncthreads();
         if (q >= a.nitems) break;
         const int item = a.order[q];
-        CgState* stp = &a.st[item];
-        if (!stp->active) continue;
-        const ResSys sy = a.sys[item / a.nrhs];
-        const int rhs = item % a.nrhs;
-        const int n1 = sy.n1, n2 = sy.n2;
-        const int n1p = (n1 + 31) & ~31, n2p = (n2 + 31) & ~31;       // 32x32 MFMA tile extents
-        const int n1k = n1p, n2k = n2p;                                 // K-loop extents (chunks of 32)
-        const int tjn = n2p / 32;
-        const int ntiles = (n1p / 32) * tjn;                            // <= 16: one tile per wave
-        const bool has_tile = wave < ntiles;
-        const int ti = has_tile ? 32 * (wave / tjn) : 0, tj = has_tile ? 32 * (wave % tjn) : 0;
-        const int l32 = lane & 31, lh = lane >> 5;
-        const int64_t base = (int64_t)a.nrhs * sy.vec_off + (int64_t)rhs * sy.n;
-        const float* K1 = a.fac32 + sy.k1_off;
-        const float* K2 = a.fac32 + sy.k2_off;
-        const float* dgv = sy.diag_off >= 0 ? a.diag32 + sy.diag_off : nullptr;
-        const float s2 = (float)sy.sigma2;
-        const bool own = orow < n1;
-        const int ncol = own ? (n2 - ocol < 16 ? (n2 - ocol > 0 ? n2 - ocol : 0) : 16) : 0;
-        float* xo = a.x + base + (int64_t)orow * n2 + ocol;     // owned x (global, updated in place)
-        const float* dgo = dgv ? dgv + orow * n2 + ocol : nullptr;
-        float* po = Ps + orow * RPS + ocol;
-        float* qo = Ts + orow * RPS + ocol;
-
-        // scalars (read by every thread; only thread 0 writes them back)
-        double rho = stp->rho, beta = stp->beta;
-        const double tol2 = stp->tol2, delta = stp->delta, rmax = stp->rmax;
-        int iters = stp->iters;
-        const int max_iters = stp->max_iters;
-        int status = stp->status, active = 1, need_update = 0;
-
-        // zero the LDS tiles over the full K-loop extent, then load p and r
-        for (int e = tid; e < n1k * RPS; e += kResThreads) {
-            Ps[e] = 0.f;
-            Ts[e] = 0.f;
-        }
-        __syncthreads();
-        for (int e = tid; e < n1 * n2; e += kResThreads) Ps[(e / n2) * RPS + (e % n2)] = a.p[base + e];
-        float rr[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) rr[j] = j < ncol ? a.r[base + (int64_t)orow * n2 + ocol + j] : 0.f;
-        __syncthreads();
-
-        // Factor chunks in the order the iteration consumes them (K2 column
-        // chunks, then K1 column chunks, then K2 again for the next iteration):
-        // every thread holds its four entries of the next chunk in registers,
-        // loaded while the current chunk's MFMAs run.  Entry u of a chunk is
-        // e = tid + u * kResThreads, row e / KC, column e % KC of the chunk.
-        const int nc2 = n2k / KC, nc1 = n1k / KC;
-        int cnext = 0;                                  // chunk the registers hold
-        float fpre[4];
-        auto fetch = [&](int c) {
-            const bool second = c >= nc2;
-            const float* K = second ? K1 : K2;
-            const int nk = second ? n1 : n2;
-            const int npad = second ? n1p : n2p;
-            const int c0 = (second ? c - nc2 : c) * KC;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = tid + u * kResThreads, rb = e / KC, kc = e % KC;
-                fpre[u] = (e < npad * KC && rb < nk && c0 + kc < nk) ? K[rb * nk + c0 + kc] : 0.f;
-            }
-        };
-        auto fetch_next = [&]() {
-            cnext = cnext + 1 == nc2 + nc1 ? 0 : cnext + 1;
-            fetch(cnext);
-        };
-        auto stage_chunk = [&](int npad) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = tid + u * kResThreads;
-                if (e < npad * KC) Fc[(e / KC) * FPS + e % KC] = fpre[u];
-            }
-        };
-        fetch(0);
-
-        for (;;) {
-            // p = r + beta p on the owned elements
-            const float bf = (float)beta;
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (j < ncol) po[j] = __builtin_fmaf(bf, po[j], rr[j]);
-            __syncthreads();
-            // T = P K2^T   (32x32 tile per wave: T[ti.., tj..] = sum_l P[ti.., l] K2[tj.., l])
-            floatx16 acc;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-            for (int l0 = 0; l0 < n2k; l0 += KC) {
-                stage_chunk(n2p);
-                __syncthreads();
-                fetch_next();                               // lands during this chunk's MFMAs
-                if (has_tile) {
-                    const float* pa = Ps + (ti + l32) * RPS + l0 + lh;
-                    const float* fb = Fc + (tj + l32) * FPS + lh;
-#pragma unroll 4
-                    for (int kk = 0; kk < KC; kk += 2)
-                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[kk], fb[kk], acc, 0, 0, 0);
-                }
-                __syncthreads();
-            }
-            if (has_tile)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    Ts[(ti + 8 * (v >> 2) + 4 * lh + (v & 3)) * RPS + tj + l32] = acc[v];
-            __syncthreads();
-            // Q = K1 T   (Q[ti.., tj..] = sum_i K1[ti.., i] T[i, tj..])
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-            for (int i0 = 0; i0 < n1k; i0 += KC) {
-                stage_chunk(n1p);
-                __syncthreads();
-                fetch_next();
-                if (has_tile) {
-                    const float* fa = Fc + (ti + l32) * FPS + lh;
-                    const float* tb = Ts + (i0 + lh) * RPS + tj + l32;
-#pragma unroll 4
-                    for (int kk = 0; kk < KC; kk += 2)
-                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[kk], tb[kk * RPS], acc, 0, 0, 0);
-                }
-                __syncthreads();
-            }
-            // stage Q over the dead T tile, then the owned-element epilogue
-            if (has_tile)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    Ts[(ti + 8 * (v >> 2) + 4 * lh + (v & 3)) * RPS + tj + l32] = acc[v];
-            __syncthreads();
-            // q = K1 T + (sigma2 + d) p;  mu = p.q
-            double mu_l = 0.0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (j < ncol) {
-                    const float pe = po[j];
-                    const float qv = qo[j] + (s2 + (dgo ? dgo[j] : 0.f)) * pe;
-                    qo[j] = qv;
-                    mu_l += (double)pe * (double)qv;
-                }
-            const double mu = block_sum16(mu_l, red_pq);
-            if (!(mu > 0.0) || !finite_d(mu)) {
-                status = finite_d(mu) ? COLA_ERR_NOT_SPD : COLA_ERR_NONFINITE;
-                active = 0;
-                break;
-            }
-            const float af = (float)(rho / mu);
-            double rho_l = 0.0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (j < ncol) {
-                    xo[j] = __builtin_fmaf(af, po[j], xo[j]);
-                    rr[j] = __builtin_fmaf(-af, qo[j], rr[j]);
-                    rho_l += (double)rr[j] * (double)rr[j];
-                }
-            const double rn = block_sum16(rho_l, red_rr);
-            ++iters;
-            bool stop = false;
-            if (!finite_d(rn)) {
-                status = COLA_ERR_NONFINITE;
-                active = 0;
-                stop = true;
-            } else if (rn <= tol2) {                 // pause; the FP64 residual decides
-                need_update = 1;
-                active = 0;
-                stop = true;
-            } else if (iters >= max_iters) {
-                status = COLA_NOT_CONVERGED;
-                active = 0;
-                stop = true;
-            } else if (rn < delta * delta * rmax * rmax) {
-                need_update = 1;
-                stop = true;
-            }
-            beta = rn / rho;
-            rho = rn;
-            if (stop) break;
-        }
-        // write the state back
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (j < ncol) a.r[base + (int64_t)orow * n2 + ocol + j] = rr[j];
-        for (int e = tid; e < n1 * n2; e += kResThreads) a.p[base + e] = Ps[(e / n2) * RPS + (e % n2)];
-        if (tid == 0) {
-            stp->rho = rho;
-            stp->beta = beta;
-            stp->iters = iters;
-            stp->status = status;
-            stp->need_update = need_update;
-            if (!active) {
-                stp->active = 0;
-                atomicSub(&a.cnt->num_active, 1);
-            }
-        }
-        __syncthreads();
+        if (!a.st[item].active) continue;
+        // four wave columns along one mode, two along the other: the deal whose fullest SIMD has fewer tiles
+        const ResSys& sy = a.sys[item / a.nrhs];
+        const int t1 = (sy.n1 + 15) / 16, t2 = (sy.n2 + 15) / 16;
+        if ((t1 + 3) / 4 * t2 <= (t2 + 3) / 4 * t1) resident_item<2, 4>(a, item, Ps, Ts, red_pq, red_rr);
+        else resident_item<4, 2>(a, item, Ps, Ts, red_pq, red_rr);
     }
 }
 
@@ -314,6 +361,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident_cg(ResArgs a) {
 // tiles (16 x 64) that share the A fragment; 16 waves per item so that four
 // waves per SIMD cover each other's L2 latency.
 constexpr int kResidThreads = 1024;
+constexpr int kResidWaves = kResidThreads / 64;
 constexpr int PX = kResMax + 2;                  // pitch of X: conflict-free A-operand reads
 
 __device__ inline doublex4 mma_f64(double a, double b, doublex4 c) {
@@ -322,7 +370,7 @@ __device__ inline doublex4 mma_f64(double a, double b, doublex4 c) {
 
 __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
     __shared__ double Xs[kResMax * PX];
-    __shared__ double red[kResWaves];
+    __shared__ double red[kResidWaves];
     const int item = blockIdx.x;
     CgState& st = a.st[item];
     if (a.all_items ? st.status == COLA_OK : !st.need_update) return;
@@ -351,7 +399,7 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
     __syncthreads();
     const int nt1 = n1p / 16, nt2 = n2p / 16, ng2 = (nt2 + 3) / 4;
     // T[i][j] = sum_l X[i][l] K2[j][l]
-    for (int g = wave; g < nt1 * ng2; g += kResWaves) {
+    for (int g = wave; g < nt1 * ng2; g += kResidWaves) {
         const int i0 = (g / ng2) * 16, j0 = (g % ng2) * 64;
         doublex4 acc[4] = {};
         for (int k = 0; k < n2p; k += 4) {
@@ -377,7 +425,7 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
     __syncthreads();                                    // T complete
     // q = K1 T + (sigma2 + d) x,  r = b - q
     double rr = 0.0;
-    for (int g = wave; g < nt1 * ng2; g += kResWaves) {
+    for (int g = wave; g < nt1 * ng2; g += kResidWaves) {
         const int i0 = (g / ng2) * 16, j0 = (g % ng2) * 64;
         doublex4 acc[4] = {};
         const int arow = i0 + lr;
@@ -407,7 +455,7 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
                 }
             }
     }
-    rr = block_sum16(rr, red);
+    rr = block_sum_once<kResidWaves>(rr, red);
     if (tid == 0) {
         st.rho_true = rr;
         if (!a.all_items) reliable_finish(st, a.cnt);
