@@ -1173,9 +1173,9 @@ int32_t ensure_resident(cola_op_s* op, int nrhs, hipStream_t st) {
     return COLA_OK;
 }
 
-// All systems at once through the resident kernel: rounds of (persistent FP32
-// CG until each item needs a reliable update) + (FP64 residual of the items
-// that asked), then one FP64 residual of every item for the final report.
+// All systems at once through the resident kernel, one launch for the whole
+// solves (FP32 CG and the FP64 residuals of its reliable updates), then the FP64
+// residual of every item without a certified one for the final report.
 int32_t solve_resident(cola_op_s* op, const double* B, double* X, int nrhs, const cola_solve_opts* o,
                        cola_solve_info* info, hipStream_t st) {
     int32_t rc = ensure_ws(op, 1, st);              // counters and pinned poll flag
@@ -1205,23 +1205,13 @@ int32_t solve_resident(cola_op_s* op, const double* B, double* X, int nrhs, cons
     HIP_TRY(fill_i32(&w.cnt->num_active, 0, 1, st));
     HIP_TRY(launch_resident_prepare(a, o->tol, o->max_iters, o->inner_tol, st));
     const int grid = std::max(1, std::min(a.nitems, op->num_cus > 0 ? op->num_cus : 256));
-    const int rounds = std::max(o->max_sweeps, 32);
-    for (int rd = 0; rd < rounds; ++rd) {
-        if (o->check_every > 0 && rd > 0) {
-            int32_t active = 0;
-            rc = poll_flag(op, &w.cnt->num_active, st, &active);
-            if (rc != COLA_OK) return rc;
-            if (active <= 0) break;
-        }
-        HIP_TRY(fill_i32((int32_t*)op->res_queue, 0, 1, st));
-        {
-            ProfScope ps(op->prof, "resident", st);
-            HIP_TRY(launch_resident_cg(a, grid, st));
-        }
-        HIP_TRY(launch_resident_resid64(a, st));
+    a.max_rounds = std::max(o->max_sweeps, 32);
+    HIP_TRY(fill_i32((int32_t*)op->res_queue, 0, 1, st));
+    {
+        ProfScope ps(op->prof, "resident", st);
+        HIP_TRY(launch_resident_cg(a, grid, st));
     }
-    a.all_items = 1;
-    HIP_TRY(launch_resident_resid64(a, st));
+    HIP_TRY(launch_resident_final(a, st));
     if (info) HIP_TRY(write_info(info, nullptr, op->res_st, a.nitems, st));
     return COLA_OK;
 }

@@ -30,14 +30,13 @@ struct ResArgs {
     double* t64;                    // packed FP64 scratch (residual intermediate)
     CgState* st;                    // per item
     SolveCounters* cnt;
-    int32_t all_items;              // residual kernel: final pass (items without a certified residual)
+    int32_t max_rounds;             // FP64 residuals of one item, at most
 };
 
 constexpr int kResMax = 128;        // largest mode size handled by the resident kernel
 
 hipError_t launch_resident_prepare(const ResArgs& a, double tol, int max_iters, double delta, hipStream_t s);
 hipError_t launch_resident_cg(const ResArgs& a, int grid, hipStream_t s);
-hipError_t launch_resident_resid64(const ResArgs& a, hipStream_t s);
-hipError_t launch_resident_info(const ResArgs& a, cola_solve_info* info, hipStream_t s);
+hipError_t launch_resident_final(const ResArgs& a, hipStream_t s);
 
 }  // namespace cola

@@ -15,15 +15,17 @@
 //     barrier separates slices: four barriers an iteration (two for the exchange
 //     of P and T, one for each dot product);
 //   - 16 x 16 tiles, dealt to the SIMDs along the mode that balances them.
-// 128 uneven systems (modes 16 to 128, up to 670 iterations), launch of one round:
-// 2.4 ms with the factors staged through LDS in 32-column chunks (two barriers a
-// chunk, x in memory, 36 us an iteration at 128 x 128), see k_resident_cg for now.
 // Workgroups pull items from an atomic queue ordered largest-first, so uneven
 // iteration counts balance across the chip, and every workgroup leaves once the
-// queue is empty.  An item leaves the kernel when its FP32 residual has dropped by
-// delta (or converged): the FP64 residual kernel then folds x into the FP64
-// solution, forms b - A x with the FP64 factors and replaces r, and the next
-// round resumes the same CG (reliable updates).
+// queue is empty.  When an item's FP32 residual has dropped by delta (or
+// converged), its workgroup folds x into the FP64 solution, forms b - A x with the
+// FP64 factors, replaces r and resumes the same CG (reliable updates), so items
+// do not wait for one another.
+// 128 uneven systems (modes 16 to 128, 216 iterations on average and up to 670),
+// two solves and their gradients: 56 ms with the factors staged through LDS in
+// 32-column chunks (two barriers a chunk, x in memory: 36 us an iteration at 128 x
+// 128), 31 ms with the iteration above, 29 ms with the residuals in the same
+// launch (before, a launch for every round of all items and one for its residuals).
 #include "resident.h"
 
 namespace cola {
@@ -31,6 +33,9 @@ namespace cola {
 constexpr int kResThreads = 512;                 // 8 waves per item
 constexpr int kResWaves = kResThreads / 64;
 constexpr int RPS = kResMax + 4;                 // LDS row stride of P and T^T (floats): conflict-free 16-byte accesses
+constexpr int PX = kResMax + 2;                  // pitch of the FP64 X: conflict-free A-operand reads
+constexpr size_t kResLds = 2 * sizeof(float) * kResMax * RPS > sizeof(double) * kResMax * PX
+                               ? 2 * sizeof(float) * kResMax * RPS : sizeof(double) * kResMax * PX;
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Sum over the WAVES waves of a workgroup with a single barrier.  A caller
@@ -326,54 +331,22 @@ __device__ inline void resident_item(const ResArgs& a, int item, float* Ps, floa
     __syncthreads();
 }
 
-__global__ __launch_bounds__(kResThreads, 2) void k_resident_cg(ResArgs a) {
-    __shared__ __attribute__((aligned(16))) float Ps[kResMax * RPS];   // direction P
-    __shared__ __attribute__((aligned(16))) float Ts[kResMax * RPS];   // (P K2^T)^T
-    __shared__ double red_pq[kResWaves];       // slots of the p.q sums
-    __shared__ double red_rr[kResWaves];       // slots of the r.r sums (every other barrier of the
-                                               // iteration lies between one sum's reads and its next write)
-    __shared__ int s_item;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(a.queue, 1u);
-        __syncthreads();
-        const int q = s_item;
-        __syncthreads();
-        if (q >= a.nitems) break;
-        const int item = a.order[q];
-        if (!a.st[item].active) continue;
-        // four wave columns along one mode, two along the other: the deal whose fullest SIMD has fewer tiles
-        const ResSys& sy = a.sys[item / a.nrhs];
-        const int t1 = (sy.n1 + 15) / 16, t2 = (sy.n2 + 15) / 16;
-        if ((t1 + 3) / 4 * t2 <= (t2 + 3) / 4 * t1) resident_item<2, 4>(a, item, Ps, Ts, red_pq, red_rr);
-        else resident_item<4, 2>(a, item, Ps, Ts, red_pq, red_rr);
-    }
-}
-
-// FP64 residual of requested items: fold the FP32 iterate into the FP64
-// solution, r = b - (K1 X K2^T + (sigma2 + d) x) with the FP64 factors,
-// r_lo = r; then the reliable-update decision.  Final pass (a.all_items):
-// every item without a certified residual (status not OK); a converged item
-// was certified by its last update and its x has not changed since.
+// FP64 residual of one item: fold the FP32 iterate into the FP64 solution,
+// r = b - (K1 X K2^T + (sigma2 + d) x) with the FP64 factors, r_lo = r; returns
+// ||r||^2 in every thread.
 // Both mode products run on the FP64 matrix cores (v_mfma_f64_16x16x4f64;
 // lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16], accumulator
-// element v sits at row 4 v + l / 16, column l % 16).  X stays in LDS (padded rows, zero beyond the system), the factors
-// and T = X K2^T come from L2.  Each wave computes groups of 1 x 4 output
-// tiles (16 x 64) that share the A fragment; 16 waves per item so that four
-// waves per SIMD cover each other's L2 latency.
-constexpr int kResidThreads = 1024;
-constexpr int kResidWaves = kResidThreads / 64;
-constexpr int PX = kResMax + 2;                  // pitch of X: conflict-free A-operand reads
+// element v sits at row 4 v + l / 16, column l % 16).  X stays in LDS (padded rows, zero beyond the
+// system), the factors and T = X K2^T come from L2.  Each wave computes groups of 1 x 4 output
+// tiles (16 x 64) that share the A fragment.
 
 __device__ inline doublex4 mma_f64(double a, double b, doublex4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-__global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
-    __shared__ double Xs[kResMax * PX];
-    __shared__ double red[kResidWaves];
-    const int item = blockIdx.x;
-    CgState& st = a.st[item];
-    if (a.all_items ? st.status == COLA_OK : !st.need_update) return;
+template <int WAVES>
+__device__ inline double resident_residual(const ResArgs& a, int item, double* Xs, double* red) {
+    constexpr int kThr = 64 * WAVES;
     const ResSys sy = a.sys[item / a.nrhs];
     const int rhs = item % a.nrhs;
     const int n1 = sy.n1, n2 = sy.n2;
@@ -385,7 +358,7 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
     const int lr = lane & 15, lk = lane >> 4;
     const int n1p = (n1 + 15) & ~15, n2p = (n2 + 15) & ~15;       // 16 x 16 tile extents
     // fold the FP32 correction into x64 and stage X (zero in the padding)
-    for (int e = tid; e < n1p * n2p; e += kResidThreads) {
+    for (int e = tid; e < n1p * n2p; e += kThr) {
         const int row = e / n2p, col = e % n2p;
         double v = 0.0;
         if (row < n1 && col < n2) {
@@ -399,7 +372,7 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
     __syncthreads();
     const int nt1 = n1p / 16, nt2 = n2p / 16, ng2 = (nt2 + 3) / 4;
     // T[i][j] = sum_l X[i][l] K2[j][l]
-    for (int g = wave; g < nt1 * ng2; g += kResidWaves) {
+    for (int g = wave; g < nt1 * ng2; g += WAVES) {
         const int i0 = (g / ng2) * 16, j0 = (g % ng2) * 64;
         doublex4 acc[4] = {};
         for (int k = 0; k < n2p; k += 4) {
@@ -425,7 +398,7 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
     __syncthreads();                                    // T complete
     // q = K1 T + (sigma2 + d) x,  r = b - q
     double rr = 0.0;
-    for (int g = wave; g < nt1 * ng2; g += kResidWaves) {
+    for (int g = wave; g < nt1 * ng2; g += WAVES) {
         const int i0 = (g / ng2) * 16, j0 = (g % ng2) * 64;
         doublex4 acc[4] = {};
         const int arow = i0 + lr;
@@ -455,12 +428,57 @@ __global__ __launch_bounds__(kResidThreads) void k_resident_resid64(ResArgs a) {
                 }
             }
     }
-    rr = block_sum_once<kResidWaves>(rr, red);
-    if (tid == 0) {
-        st.rho_true = rr;
-        if (!a.all_items) reliable_finish(st, a.cnt);
+    return block_sum_once<WAVES>(rr, red);
+}
+
+// Every item from the queue to its end: iterations until it asks for an FP64 residual, the residual
+// and the reliable-update decision, and on until it is finished (or max_rounds residuals were formed).
+__global__ __launch_bounds__(kResThreads, 2) void k_resident_cg(ResArgs a) {
+    __shared__ __attribute__((aligned(16))) char smem[kResLds];
+    float* Ps = (float*)smem;                  // direction P
+    float* Ts = Ps + kResMax * RPS;            // (P K2^T)^T
+    __shared__ double red_pq[kResWaves];       // slots of the p.q sums
+    __shared__ double red_rr[kResWaves];       // slots of the r.r sums (every other barrier of the
+                                               // iteration lies between one sum's reads and its next write)
+    __shared__ int s_item;
+    for (;;) {
+        if (threadIdx.x == 0) s_item = (int)atomicAdd(a.queue, 1u);
+        __syncthreads();
+        const int q = s_item;
+        __syncthreads();
+        if (q >= a.nitems) break;
+        const int item = a.order[q];
+        if (!a.st[item].active) continue;
+        // four wave columns along one mode, two along the other: the deal whose fullest SIMD has fewer tiles
+        const ResSys& sy = a.sys[item / a.nrhs];
+        const int t1 = (sy.n1 + 15) / 16, t2 = (sy.n2 + 15) / 16;
+        const bool wide = (t1 + 3) / 4 * t2 <= (t2 + 3) / 4 * t1;
+        for (int round = 0; round < a.max_rounds; ++round) {
+            if (wide) resident_item<2, 4>(a, item, Ps, Ts, red_pq, red_rr);
+            else resident_item<4, 2>(a, item, Ps, Ts, red_pq, red_rr);
+            if (!a.st[item].need_update) break;            // the iteration limit, or a breakdown
+            const double rr = resident_residual<kResWaves>(a, item, (double*)smem, red_rr);
+            if (threadIdx.x == 0) {
+                a.st[item].rho_true = rr;
+                reliable_finish(a.st[item], a.cnt);
+            }
+            __syncthreads();
+            if (!a.st[item].active) break;
+        }
     }
 }
+
+// Final pass: the true residual of the items without a certified one (status not OK); a converged
+// item was certified by its last update and its x has not changed since.
+constexpr int kResidWaves = 16;
+__global__ __launch_bounds__(64 * kResidWaves) void k_resident_final(ResArgs a) {
+    __shared__ double Xs[kResMax * PX];
+    __shared__ double red[kResidWaves];
+    if (a.st[blockIdx.x].status == COLA_OK) return;
+    const double rr = resident_residual<kResidWaves>(a, blockIdx.x, Xs, red);
+    if (threadIdx.x == 0) a.st[blockIdx.x].rho_true = rr;
+}
+
 
 hipError_t launch_resident_prepare(const ResArgs& a, double tol, int max_iters, double delta, hipStream_t s) {
     hipLaunchKernelGGL(k_resident_prepare, dim3(a.nitems), dim3(kThreads), 0, s, a, tol, max_iters, delta);
@@ -470,8 +488,8 @@ hipError_t launch_resident_cg(const ResArgs& a, int grid, hipStream_t s) {
     hipLaunchKernelGGL(k_resident_cg, dim3(grid), dim3(kResThreads), 0, s, a);
     return hipGetLastError();
 }
-hipError_t launch_resident_resid64(const ResArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_resident_resid64, dim3(a.nitems), dim3(kResidThreads), 0, s, a);
+hipError_t launch_resident_final(const ResArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_resident_final, dim3(a.nitems), dim3(64 * kResidWaves), 0, s, a);
     return hipGetLastError();
 }
 
