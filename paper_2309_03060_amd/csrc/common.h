@@ -5,6 +5,8 @@
 #include <hip/hip_bf16.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/cola.h"
 
 namespace cola {
@@ -84,9 +86,38 @@ struct SolveCounters {
 
 // ---------------------------------------------------------------------------
 // Wave / block reductions (fixed order, hence deterministic).
+//
+// Sum over the 16 lanes of a DPP row, valid in each of them.  Lane moves inside the vector ALU: a
+// shuffle through the LDS pipe (two ds_bpermute a step for a double) costs over 100 cycles of latency.
+__device__ inline double row_sum16(double v) {
+    auto add = [](double x, auto ctrl) {
+        constexpr int c = decltype(ctrl)::value;
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, c, 0xf, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), c, 0xf, 0xf, true);
+        return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    };
+    v = add(v, std::integral_constant<int, 0xB1>{});        // lane ^ 1 (quad_perm 1, 0, 3, 2)
+    v = add(v, std::integral_constant<int, 0x4E>{});        // lane ^ 2 (quad_perm 2, 3, 0, 1)
+    v = add(v, std::integral_constant<int, 0x141>{});       // the other quad of eight (row_half_mirror)
+    return add(v, std::integral_constant<int, 0x140>{});    // the other eight (row_mirror)
+}
+
+// Sum over the 64 lanes of a wave, valid in each of them.  The four rows meet through the lane swaps:
+// with both operands v, permlane16_swap leaves rows (0, 0, 2, 2) and (1, 1, 3, 3), permlane32_swap
+// the lower and the upper half twice.
 __device__ inline double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = row_sum16(v);
+    uint64_t b = __builtin_bit_cast(uint64_t, v);
+    auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    v = __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+        __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    b = __builtin_bit_cast(uint64_t, v);
+    lo = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+    hi = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
 }
 
 // Sum over the 256 threads of a block; the result is valid in every thread.

@@ -11,7 +11,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <type_traits>
 #include <vector>
 
 #include "vector.h"
@@ -74,21 +73,6 @@ __global__ void k_jacobi_init(const double* A, double* U, double* V, int64_t n) 
         U[e] = A[e];
         V[e] = (e / n == e % n) ? 1.0 : 0.0;
     }
-}
-
-// Sum over the 16 lanes of a DPP row, valid in each of them.
-__device__ inline double row_sum16(double v) {
-    auto add = [](double x, auto ctrl) {
-        constexpr int c = decltype(ctrl)::value;
-        const uint64_t b = __builtin_bit_cast(uint64_t, x);
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, c, 0xf, 0xf, true);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), c, 0xf, 0xf, true);
-        return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-    };
-    v = add(v, std::integral_constant<int, 0xB1>{});        // lane ^ 1 (quad_perm 1, 0, 3, 2)
-    v = add(v, std::integral_constant<int, 0x4E>{});        // lane ^ 2 (quad_perm 2, 3, 0, 1)
-    v = add(v, std::integral_constant<int, 0x141>{});       // the other quad of eight (row_half_mirror)
-    return add(v, std::integral_constant<int, 0x140>{});    // the other eight (row_mirror)
 }
 
 // One pair of columns of U in LDS by 16 lanes (lane l: rows l, l + 16, ..; R of them): rotate them
