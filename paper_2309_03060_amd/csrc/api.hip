@@ -831,8 +831,12 @@ int32_t run_cg(cola_op_s* op, const SysInfo& s, int prec, int nrhs, T* x, T* r, 
 
 int32_t ensure_eig(cola_op_s* op, hipStream_t st);
 
-// Scratch of the Kronecker-eigen transforms (at least `need` doubles).
-int32_t ensure_eig_tmp(cola_op_s* op, int64_t need, hipStream_t st) {
+// Scratch of the Kronecker-eigen transforms for nrhs right-hand sides: the transformed vectors, then
+// the two intermediates of the eigenvector operators' products (one term each), which need no CG
+// workspace of their own (eighteen buffers of nrhs * nmax doubles that took longer to free than a
+// direct solve takes).
+int32_t ensure_eig_tmp(cola_op_s* op, int nrhs, hipStream_t st) {
+    const int64_t need = (int64_t)nrhs * (op->n_total + 2 * op->nmax + 4);
     if (op->eig_tmp_elems >= need) return COLA_OK;
     (void)hipStreamSynchronize(st);
     if (op->eig_tmp) dev_free(op, op->eig_tmp);
@@ -841,6 +845,19 @@ int32_t ensure_eig_tmp(cola_op_s* op, int64_t need, hipStream_t st) {
     if (dev_alloc(op, (void**)&op->eig_tmp, sizeof(double) * need) != COLA_OK) return COLA_ERR_OOM;
     op->eig_tmp_elems = need;
     return COLA_OK;
+}
+
+// y = (Q^T or Q of system si) x, with the intermediates in the scratch of `op`.
+int32_t eig_transform(cola_op_s* op, cola_op_s* sub, size_t si, int nrhs, const double* x, double* y,
+                      hipStream_t st) {
+    auto even = [](int64_t n) { return (n + 1) & ~(int64_t)1; };          // 16-byte aligned
+    double* i0 = op->eig_tmp + even((int64_t)nrhs * op->n_total);
+    void* const inter[2] = {i0, i0 + even((int64_t)nrhs * op->nmax)};
+    PassArgs a;
+    std::memset(&a, 0, sizeof(a));                       // a product needs no reduction buffers
+    a.epi = EPI_MATVEC;
+    a.Ep = x;
+    return enqueue_mvm(sub, sub->sys[si], COLA_PREC_FP64, nrhs, x, nullptr, y, a, st, inter, &sub->prof);
 }
 
 // One system's operator as plain pointers into the FP64 master copy.
@@ -897,23 +914,12 @@ int32_t ensure_precond(cola_op_s* op, int kind, hipStream_t st) {
 int32_t apply_kron_eig(cola_op_s* op, size_t si, int nrhs, const double* r, double* z, hipStream_t st) {
     const SysInfo& s = op->sys[si];
     double* y = op->eig_tmp;
-    for (int step = 0; step < 2; ++step) {
-        cola_op_s* sub = step == 0 ? op->eig_qt : op->eig_q;
-        int32_t rc = ensure_ws(sub, nrhs, st);
-        if (rc != COLA_OK) return rc;
-        PassArgs a = base_args(sub);
-        a.epi = EPI_MATVEC;
-        a.Ep = step == 0 ? (const void*)r : (const void*)y;
-        rc = enqueue_mvm(sub, sub->sys[si], COLA_PREC_FP64, nrhs, a.Ep, nullptr, step == 0 ? (void*)y : (void*)z,
-                         a, st);
-        if (rc != COLA_OK) return rc;
-        if (step == 0) {
-            const double* lam[3] = {nullptr, nullptr, nullptr};
-            for (int k = 0; k < s.Fv; ++k) lam[k] = op->eig_lam + op->eig_lam_off[si][k];
-            HIP_TRY(eig_scale(y, y, nrhs, s.Fv, s.dims, lam, op->pc_shift[si], st));
-        }
-    }
-    return COLA_OK;
+    int32_t rc = eig_transform(op, op->eig_qt, si, nrhs, r, y, st);
+    if (rc != COLA_OK) return rc;
+    const double* lam[3] = {nullptr, nullptr, nullptr};
+    for (int k = 0; k < s.Fv; ++k) lam[k] = op->eig_lam + op->eig_lam_off[si][k];
+    HIP_TRY(eig_scale(y, y, nrhs, s.Fv, s.dims, lam, op->pc_shift[si], st));
+    return eig_transform(op, op->eig_q, si, nrhs, y, z, st);
 }
 
 // r64 = B - A x with the FP64 factors for every right-hand side, ||r64||^2 into cg.rho_true.
@@ -952,7 +958,7 @@ int32_t run_pcg(cola_op_s* op, const SysInfo& s, const double* B, double* X, int
     int32_t rc = ensure_precond(op, o->precond, st);
     if (rc != COLA_OK) return rc;
     if (o->precond == COLA_PRECOND_KRON_EIG) {
-        rc = ensure_eig_tmp(op, (int64_t)nrhs * n, st);
+        rc = ensure_eig_tmp(op, nrhs, st);
         if (rc != COLA_OK) return rc;
     }
     double* x = (double*)w.vx;
@@ -1654,18 +1660,21 @@ int32_t cola_eig_solve(cola_op_t op, const double* B, double* X, int32_t nrhs, v
     hipStream_t st = S(stream);
     int32_t rc = ensure_eig(op, st);
     if (rc != COLA_OK) return rc;
-    rc = ensure_eig_tmp(op, (int64_t)nrhs * op->n_total, st);
-    if (rc != COLA_OK) return rc;
-    rc = cola_kron_matvec(op->eig_qt, B, op->eig_tmp, nrhs, COLA_F64, COLA_PREC_FP64, stream);
+    rc = ensure_eig_tmp(op, nrhs, st);
     if (rc != COLA_OK) return rc;
     for (size_t i = 0; i < op->sys.size(); ++i) {
         const SysInfo& s = op->sys[i];
         const double* lam[3] = {nullptr, nullptr, nullptr};
         for (int k = 0; k < s.Fv; ++k) lam[k] = op->eig_lam + op->eig_lam_off[i][k];
-        double* y = op->eig_tmp + (int64_t)nrhs * s.vec_off;
+        const int64_t off = (int64_t)nrhs * s.vec_off;
+        double* y = op->eig_tmp + off;
+        rc = eig_transform(op, op->eig_qt, i, nrhs, B + off, y, st);
+        if (rc != COLA_OK) return rc;
         HIP_TRY(eig_scale(y, y, nrhs, s.Fv, s.dims, lam, s.sigma2, st));
+        rc = eig_transform(op, op->eig_q, i, nrhs, y, X + off, st);
+        if (rc != COLA_OK) return rc;
     }
-    return cola_kron_matvec(op->eig_q, op->eig_tmp, X, nrhs, COLA_F64, COLA_PREC_FP64, stream);
+    return COLA_OK;
 }
 
 int32_t cola_op_memory(cola_op_t op, int64_t* live_bytes, int64_t* peak_bytes, int32_t reset_peak) {
