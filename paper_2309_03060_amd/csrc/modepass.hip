@@ -31,13 +31,13 @@ struct ModeF64 {
     using V = double; using Acc = doublex4;
     typedef double Vec __attribute__((ext_vector_type(2)));                     // 16 bytes
     typedef double VecU __attribute__((ext_vector_type(2), aligned(8)));        // the same at element alignment
-    static constexpr int VW = 2, KB = 16, NPAD = 16;     // 128-byte k slices; panel pitch 32 (mod 64) banks
+    static constexpr int VW = 2, KT = 16, NPAD = 16;     // 128-byte k slices; panel pitch 32 (mod 64) banks
 };
 struct ModeF32 {
     using V = float; using Acc = floatx4;
     typedef float Vec __attribute__((ext_vector_type(4)));
     typedef float VecU __attribute__((ext_vector_type(4), aligned(4)));
-    static constexpr int VW = 4, KB = 32, NPAD = 16;
+    static constexpr int VW = 4, KT = 32, NPAD = 16;
 };
 
 // acc += A-row fragment x B-column fragment.  FP64: element v of a lane is row 4 v + lane / 16,
@@ -67,12 +67,13 @@ __device__ inline uint32_t xcd_order(uint32_t b, uint32_t T) {
 constexpr int mode_waves(int wm, int wn) { return wm + wn <= 4 ? 4 : (wm + wn <= 5 ? 3 : (wm * wn <= 8 ? 2 : 1)); }
 
 // ROWS or COLS layout; PNEW (ROWS): the vector operand is R + beta X; FULL (COLS): an epilogue with
-// operands, not EPI_STORE; ELEM: vectors loaded by elements (fewer elements in all than one vector).
-template <class P, int WM, int WN, bool ROWS, bool PNEW, bool FULL, bool ELEM>
+// operands, not EPI_STORE; GENERAL: 64-bit indexes and
+// element loads, for inputs of fewer elements than one vector and tiles that span 2 GB.
+template <class P, int WM, int WN, bool ROWS, bool PNEW, bool FULL, bool GENERAL>
 __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs a, uint32_t nMt, uint32_t nNt, uint32_t total) {
     using V = typename P::V; using Acc = typename P::Acc; using Vec = typename P::Vec; using VecU = typename P::VecU;
     constexpr int MT = 32 * WM, NT = 32 * WN, VW = P::VW;
-    constexpr int KT = P::KB;
+    constexpr int KT = P::KT;
     constexpr int KP = KT + VW;                              // pitch of a k-contiguous row: 4 (mod 64) banks
     constexpr int NTP = NT + P::NPAD;                        // pitch of a COLS panel row
     constexpr int A_EL = MT * KP, B_EL = ROWS ? NT * KP : KT * NTP;
@@ -113,103 +114,110 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     }
     const int64_t Mrows = ROWS ? a.G : nk;                   // rows and columns of the output matrix
     const int64_t Ncols = ROWS ? nk : a.B;
-    // This thread's vectors.  Every address is clamped into its buffer so that a slice is loaded
-    // without branches (a branch would make the compiler wait for the loads in flight); what a clamp
-    // moved, and what lies beyond nk, is put right on the way to LDS.  Rows of the output tile beyond
-    // the matrix repeat its last row and columns beyond it hold other elements: neither is stored.
-    // Factor vectors may run past the end of their matrix by part of a slice (the factor buffers
-    // are padded by a slice's 128 bytes).
-    const int64_t x_end = (ROWS ? a.G * nk : a.G * nk * a.B) - (ELEM ? 1 : VW);   // last vector of the input
+    // This thread's vectors, as 32-bit byte offsets from a uniform base that moves from slice to slice.
+    // Nothing branches between a slice's loads (a branch would make the compiler wait for the loads in
+    // flight).  Only the last slice can leave its buffers; it has offsets of its own, clamped: rows of a
+    // panel beyond nk repeat row nk - 1, and a vector past the end of the input is read early.  What a
+    // clamp moved, and what lies beyond nk, is put right on the way to LDS.  Rows of the output tile
+    // beyond the matrix repeat its last row and columns beyond it hold other elements: neither is
+    // stored.  Factor vectors may run past the end of their matrix by part of a slice (the factor
+    // buffers are padded by a slice's 128 bytes).
+    constexpr int ES = sizeof(V);
+    const int k_last = (ns - 1) * KT;                        // k0 of a term's last slice
     const int arow0 = tid / RV, akc = (tid % RV) * VW;       // k-contiguous vector q: row arow0 + q (256 / RV)
     constexpr int RQ = kThreads / RV;
-    int64_t aoff[AV];
+    constexpr int PR = NT / VW, PQ = kThreads / PR;          // COLS: vectors per panel row, rows per step of q
+    const int bk0 = tid / PR, bn = (tid % PR) * VW;
+    // the input from the tile's base (ROWS: row m0, COLS: column n0 of batch g): its last vector
+    const int64_t x_base = ROWS ? m0 * nk : g * nk * a.B + n0;
+    const int64_t x_end = (ROWS ? a.G * nk : a.G * nk * a.B) - (GENERAL ? 1 : VW) - x_base;
+    const int64_t xstep = ROWS ? KT : (int64_t)KT * a.B;
+    const int64_t x_end_last = x_end - (int64_t)(ns - 1) * xstep;        // from the base of the last slice
+    auto row_at = [&](int q, int64_t first, int64_t rows) {              // of tile row arow0 + q RQ, clamped
+        const int64_t m = first + arow0 + q * RQ;
+        return (m < rows ? m : rows - 1) - first;
+    };
+    // element offsets of vector q of the input: in a slice, and in the last one before its clamp to the end
+    auto in_off = [&](int q) -> int64_t {
+        return ROWS ? row_at(q, m0, Mrows) * nk + akc : (int64_t)(bk0 + q * PQ) * a.B + bn;
+    };
+    auto in_off_last = [&](int q) -> int64_t {
+        if constexpr (ROWS) return in_off(q);
+        const int k = bk0 + q * PQ;
+        return (int64_t)(k_last + k < nk ? k : nk - 1 - k_last) * a.B + bn;
+    };
+    constexpr int XV = ROWS ? AV : BV, FV = ROWS ? BV : AV;  // vectors of the input and of the factor
+    uint32_t xoff[XV], xlast[XV], foff[FV];
 #pragma unroll
-    for (int q = 0; q < AV; ++q) {
-        int64_t m = m0 + arow0 + q * RQ;
-        if (m >= Mrows) m = Mrows - 1;
-        aoff[q] = m * nk + akc;
+    for (int q = 0; q < XV; ++q) {
+        const int64_t l = in_off_last(q);
+        xoff[q] = (uint32_t)(in_off(q) * ES);
+        xlast[q] = (uint32_t)(((l < x_end_last ? l : x_end_last) + VW) * ES);   // from VW elements before it
     }
+#pragma unroll
+    for (int q = 0; q < FV; ++q)
+        foff[q] = (uint32_t)((row_at(q, ROWS ? n0 : m0, nk) * nk + akc) * ES);
     double beta[PNEW ? AV : 1];
     if constexpr (PNEW) {
 #pragma unroll
-        for (int q = 0; q < AV; ++q) {
-            const int64_t m = m0 + arow0 + q * RQ;
-            beta[q] = a.cg[rhs_of(a, m < Mrows ? m : Mrows - 1)].beta;
-        }
+        for (int q = 0; q < AV; ++q) beta[q] = a.cg[rhs_of(a, m0 + row_at(q, m0, Mrows))].beta;
     }
-    constexpr int PR = NT / VW, PQ = kThreads / PR;          // COLS: vectors per panel row, rows per step of q
-    const int bk0 = tid / PR, bn = (tid % PR) * VW;
-    int64_t boff[BV];                                        // ROWS: factor rows; COLS: panel rows from row 0
-    const int64_t pan = (g * nk) * a.B + n0 + bn, last_row = (int64_t)(nk - 1) * a.B;
-#pragma unroll
-    for (int q = 0; q < BV; ++q) {
-        if constexpr (ROWS) {
-            int64_t n = n0 + arow0 + q * RQ;
-            if (n >= nk) n = nk - 1;
-            boff[q] = n * nk + akc;
-        } else {
-            boff[q] = (int64_t)(bk0 + q * PQ) * a.B;
-        }
-    }
-    // the one block row / batch whose vectors can reach the end of the input
-    const bool tail = ROWS ? m0 + MT >= a.G : g == a.G - 1;
+    // whether some vector of the last slice was read early
+    const bool tail = x_end_last < (ROWS ? (int64_t)(MT - 1) * nk + KT : (int64_t)(nk - 1 - k_last) * a.B + NT);
 
     struct Slice { Vec a[AV], r[PNEW ? AV : 1], b[BV]; };
-    auto ld_factor = [&](const V* p) -> Vec { return *(const VecU*)p; };
-    auto ld_input = [&](const V* p, int64_t i, int64_t end) -> Vec {
-        if constexpr (ELEM) {
-            Vec v;
+    auto ldv = [&](const char* base, uint32_t off) -> Vec { return *(const VecU*)(base + off); };
+    // GENERAL: 64-bit indexes, by elements
+    auto ld_elem = [&](const V* base, int64_t i, int64_t end) -> Vec {
+        Vec v;
 #pragma unroll
-            for (int c = 0; c < VW; ++c) v[c] = p[i + c < end ? i + c : end];
-            return v;
-        } else {
-            return *(const VecU*)(p + i);
-        }
+        for (int c = 0; c < VW; ++c) v[c] = base[i + c < end ? i + c : end];
+        return v;
     };
-    // The slice the next load takes, advanced without divisions: its operands' bases, the elements
-    // from its base to the last panel row and to the last vector of the input, and k0.
-    const V* Kl = (const V*)a.K + (a.nsum > 1 ? 0 : (int64_t)tout * a.k_tstride);
-    const V* Xl = (const V*)a.X + (a.nsum > 1 ? 0 : (int64_t)tout * a.x_tstride);
-    const V* Rl = (const V*)a.R + (a.nsum > 1 ? 0 : (int64_t)tout * a.x_tstride);
-    const int64_t xstep = ROWS ? KT : (int64_t)KT * a.B;
-    int64_t to_row = last_row, to_end = x_end;
+    // the slice the next load takes: bases of its operands, k0
+    const int64_t t0 = a.nsum > 1 ? 0 : tout;
+    const char* Fl = (const char*)((const V*)a.K + t0 * a.k_tstride + (ROWS ? n0 : m0) * nk);
+    const char* Xl = (const char*)((const V*)a.X + t0 * a.x_tstride + x_base);
+    const char* Rl = (const char*)((const V*)a.R + t0 * a.x_tstride + x_base);
     int kl = 0, left = steps;
     auto load_slice = [&](Slice& v) {
         // past the last slice every lane loads one address (nothing uses it)
-        const int64_t keep = left > 0 ? -1 : 0;
+        const uint32_t keep = left > 0 ? 0xffffffffu : 0u;
+        const bool last = kl == k_last;
+        auto& vx = [&]() -> auto& { if constexpr (ROWS) return v.a; else return v.b; }();
+        auto& vf = [&]() -> auto& { if constexpr (ROWS) return v.b; else return v.a; }();
+        if constexpr (GENERAL) {
+            const int64_t end = x_end - (int64_t)(kl / KT) * xstep;
 #pragma unroll
-        for (int q = 0; q < AV; ++q) {
-            int64_t i = aoff[q];
-            if constexpr (ROWS) i = i < to_end ? i : to_end;
-            if constexpr (ROWS) v.a[q] = ld_input(Xl, i & keep, to_end);
-            else v.a[q] = ld_factor(Kl + (i & keep));
-            if constexpr (PNEW) v.r[q] = ld_input(Rl, i & keep, to_end);
-        }
-#pragma unroll
-        for (int q = 0; q < BV; ++q) {
-            int64_t i = boff[q];
-            if constexpr (!ROWS) {
-                i = pan + (i < to_row ? i : to_row);         // rows beyond nk read row nk - 1
-                i = i < to_end ? i : to_end;
+            for (int q = 0; q < XV; ++q) {
+                const int64_t i = left > 0 ? (last ? in_off_last(q) : in_off(q)) : 0;
+                vx[q] = ld_elem((const V*)Xl, i, end);
+                if constexpr (PNEW) v.r[q] = ld_elem((const V*)Rl, i, end);
             }
-            if constexpr (ROWS) v.b[q] = ld_factor(Kl + (i & keep));
-            else v.b[q] = ld_input(Xl, i & keep, to_end);
+#pragma unroll
+            for (int q = 0; q < FV; ++q)
+                vf[q] = *(const VecU*)((const V*)Fl + (left > 0 ? row_at(q, ROWS ? n0 : m0, nk) * nk + akc : 0));
+        } else {
+            const int back = last && left > 0 ? VW * ES : 0;
+#pragma unroll
+            for (int q = 0; q < XV; ++q) {
+                const uint32_t o = (last ? xlast[q] : xoff[q]) & keep;
+                vx[q] = ldv(Xl - back, o);
+                if constexpr (PNEW) v.r[q] = ldv(Rl - back, o);
+            }
+#pragma unroll
+            for (int q = 0; q < FV; ++q) vf[q] = ldv(Fl, foff[q] & keep);
         }
-        --left;
+        if (--left <= 0) return;                             // the bases stay on the last slice
         kl += KT;
-        if (kl < nk) {
-            Kl += KT;
-            Xl += xstep;
-            if constexpr (PNEW) Rl += xstep;
-            to_row -= xstep;
-            to_end -= xstep;
-        } else if (left > 0) {                               // the next term
-            const int64_t back = (int64_t)(ns - 1);
-            Kl += a.k_tstride - back * KT;
-            Xl += a.x_tstride - back * xstep;
-            if constexpr (PNEW) Rl += a.x_tstride - back * xstep;
-            to_row = last_row;
-            to_end = x_end;
+        if (!last) {
+            Fl += KT * ES;
+            Xl += xstep * ES;
+            if constexpr (PNEW) Rl += xstep * ES;
+        } else {                                             // the next term
+            Fl += (a.k_tstride - k_last) * ES;
+            Xl += (a.x_tstride - (int64_t)(ns - 1) * xstep) * ES;
+            if constexpr (PNEW) Rl += (a.x_tstride - (int64_t)(ns - 1) * xstep) * ES;
             kl = 0;
         }
     };
@@ -228,21 +236,14 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     int ks = 0;                                              // k0 of the slice stored next
     auto store_slice = [&](Slice& v, V* As, V* Bs) {
         const int k0 = ks;
-        ks = ks + KT < nk ? ks + KT : 0;
-        if (tail && !ELEM) {
-            if constexpr (ROWS) {
+        ks = k0 == k_last ? 0 : k0 + KT;
+        if (!GENERAL && tail && k0 == k_last) {
 #pragma unroll
-                for (int q = 0; q < AV; ++q) {
-                    unshift(v.a[q], aoff[q] + k0 - x_end);
-                    if constexpr (PNEW) unshift(v.r[q], aoff[q] + k0 - x_end);
-                }
-            } else {
-                const int64_t kB = (int64_t)k0 * a.B;
-#pragma unroll
-                for (int q = 0; q < BV; ++q) {
-                    const int64_t row = boff[q] + kB;
-                    unshift(v.b[q], pan + (row < last_row ? row : last_row) - x_end);
-                }
+            for (int q = 0; q < XV; ++q) {
+                const int64_t sh = in_off_last(q) - x_end_last;
+                if constexpr (ROWS) unshift(v.a[q], sh);
+                else unshift(v.b[q], sh);
+                if constexpr (PNEW) unshift(v.r[q], sh);
             }
         }
         if constexpr (PNEW) {
@@ -442,20 +443,28 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     }
 }
 
-template <class P, int WM, int WN, bool ROWS, bool PNEW, bool FULL, bool ELEM>
+template <class P, int WM, int WN, bool ROWS, bool PNEW, bool FULL, bool GENERAL>
 hipError_t launch_v(const PassArgs& a, hipStream_t s) {
     const int64_t M = ROWS ? a.G : a.nk, N = ROWS ? a.nk : a.B;
     const int64_t nMt = (M + 32 * WM - 1) / (32 * WM), nNt = (N + 32 * WN - 1) / (32 * WN);
     const int64_t total = nMt * nNt * a.nout * (ROWS ? 1 : a.G);
     if (total < 1 || total > 0x7fffffff || (!ROWS && a.G > 0x7fffffff)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_mode<P, WM, WN, ROWS, PNEW, FULL, ELEM>), dim3((unsigned)total), dim3(kThreads), 0, s, a,
+    hipLaunchKernelGGL((k_mode<P, WM, WN, ROWS, PNEW, FULL, GENERAL>), dim3((unsigned)total), dim3(kThreads), 0, s, a,
                        (uint32_t)nMt, (uint32_t)nNt, (uint32_t)total);
     return hipGetLastError();
 }
 
+// Fewer elements than one vector, or 128 rows (a slice of panel rows) that span 2 GB.
+template <class P>
+bool needs_general(bool rows, const PassArgs& a) {
+    const int64_t es = sizeof(typename P::V), span = ((int64_t)128 * a.nk + 128) * es;
+    return (rows ? a.G * a.nk : a.G * a.nk * a.B) < P::VW || span > 0x7fffffff ||
+           (!rows && ((int64_t)P::KT * a.B + 128) * es > 0x7fffffff);
+}
+
 template <class P, int WM, int WN, bool ROWS>
 hipError_t launch_t(const PassArgs& a, hipStream_t s) {
-    const bool elem = (ROWS ? a.G * a.nk : a.G * a.nk * a.B) < P::VW;
+    const bool elem = needs_general<P>(ROWS, a);
     if constexpr (ROWS) {
         if constexpr (WM == 1 && WN == 1)
             if (elem) return a.pnew ? launch_v<P, 1, 1, true, true, false, true>(a, s)
@@ -479,7 +488,7 @@ int trim(int w, int64_t nk) {
 
 template <class P>
 hipError_t launch_p(bool rows, const PassArgs& a, TileCfg c, hipStream_t s) {
-    if ((rows ? a.G * a.nk : a.G * a.nk * a.B) < P::VW) c = TileCfg{1, 1};   // the only tile with element loads
+    if (needs_general<P>(rows, a)) c = TileCfg{1, 1};        // the only tile built that way
     if (rows) {
         const int wn = trim(c.wn, a.nk);
 #define COLA_ROWS(M, N) \
@@ -504,10 +513,12 @@ hipError_t launch_p(bool rows, const PassArgs& a, TileCfg c, hipStream_t s) {
 
 // Tiles of few outputs load more per product; tiles of many leave CUs without blocks and pad the
 // edges.  The cost of a tile is its products, its loads (one row or column panel each) and a fixed
-// part, times the number of blocks, of which fewer than four per CU take as long as four.  Measured
-// (us, 256 CUs): 97 x 8989 outputs, K = 97, 4 batches, FP64: 32x32 37, 64x32 33, 64x64 35, 128x64 47;
-// 200 x 180, K = 200, 16 batches, FP64: 32x32 16, 64x32 18, 64x64 20, 128x128 51; 64 x 64, K = 64,
-// 2048 batches, FP32: 32x32 25, 64x32 22, 64x64 21, 128x64 29.
+// part, times the number of blocks, of which fewer than four per CU take as long as four; tiles over
+// 64 x 64 leave room for fewer blocks on a CU (a factor of 1.3).  Measured (us with the events around
+// a launch, 256 CUs): 97 x 8989 outputs, K = 97, 4 batches, FP64: 32x32 37, 64x32 33, 64x64 35, 128x64
+// 48; 200 x 180, K = 200, 16 batches, FP64: 32x32 16, 64x32 17, 64x64 20, 128x128 51; 64 x 4096, K =
+// 64, 32 batches, FP64: 64x32 45, 64x64 42, 64x128 48; 64 x 64, K = 64, 2048 batches, FP32: 32x32 24,
+// 64x32 21, 64x64 21, 128x64 29.
 TileCfg mode_tile(bool rows, int64_t nk, int64_t M, int64_t N, int64_t batch) {
     TileCfg best{1, 1};
     double cost = 1e300;
@@ -516,7 +527,7 @@ TileCfg mode_tile(bool rows, int64_t nk, int64_t M, int64_t N, int64_t batch) {
             const int m = rows ? wm : trim(wm, nk), n = rows ? trim(wn, nk) : wn;
             const double blocks = (double)((M + 32 * m - 1) / (32 * m)) * (double)((N + 32 * n - 1) / (32 * n)) *
                                   (double)batch;
-            const double c = std::max(blocks, 1024.0) * (m * n + m + n + 1);
+            const double c = std::max(blocks, 1024.0) * (m * n + m + n + 1) * (m * n > 4 ? 1.3 : 1.0);
             if (c < cost) {
                 cost = c;
                 best = TileCfg{wm, wn};
