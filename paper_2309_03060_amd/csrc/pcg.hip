@@ -16,6 +16,8 @@
 namespace cola {
 namespace {
 
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // right-hand side g starts at g * n, any n
+
 __device__ inline double diag_entry(const DiagArgs& a, int64_t i) {
     int64_t idx[3] = {0, 0, 0};
     int64_t rem = i;
@@ -76,10 +78,23 @@ __global__ __launch_bounds__(kThreads) void k_pcg_update(double* x, double* r, c
     const double* pg = p + g * n;
     const double* qg = q + g * n;
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
-        xg[i] = fma(alpha, pg[i], xg[i]);
-        const double rv = fma(-alpha, qg[i], rg[i]);
-        rg[i] = rv;
+    const int64_t first = (int64_t)blockIdx.x * kThreads + threadIdx.x, stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t i = first; i < n / 2; i += stride) {
+        d2u xv = ((d2u*)xg)[i], rv = ((d2u*)rg)[i];
+        const d2u pv = ((const d2u*)pg)[i], qv = ((const d2u*)qg)[i];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            xv[c] = fma(alpha, pv[c], xv[c]);
+            rv[c] = fma(-alpha, qv[c], rv[c]);
+            s += rv[c] * rv[c];
+        }
+        ((d2u*)xg)[i] = xv;
+        ((d2u*)rg)[i] = rv;
+    }
+    if ((n & 1) && first == 0) {
+        xg[n - 1] = fma(alpha, pg[n - 1], xg[n - 1]);
+        const double rv = fma(-alpha, qg[n - 1], rg[n - 1]);
+        rg[n - 1] = rv;
         s += rv * rv;
     }
     s = block_sum(s, red);
@@ -112,16 +127,21 @@ __global__ __launch_bounds__(kThreads) void k_pcg_precond_dot(const double* r, d
     const double* rg = r + g * n;
     double* zg = z + g * n;
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
-        const double rv = rg[i];
-        double zv;
-        if (dinv) {
-            zv = dinv[i] * rv;
-            zg[i] = zv;
-        } else {
-            zv = zg[i];
+    const int64_t first = (int64_t)blockIdx.x * kThreads + threadIdx.x, stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t i = first; i < n / 2; i += stride) {
+        const d2u rv = ((const d2u*)rg)[i];
+        d2u zv = dinv ? ((const d2u*)dinv)[i] : ((const d2u*)zg)[i];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (dinv) zv[c] *= rv[c];
+            s += rv[c] * zv[c];
         }
-        s += rv * zv;
+        if (dinv) ((d2u*)zg)[i] = zv;
+    }
+    if ((n & 1) && first == 0) {
+        const double zv = dinv ? dinv[n - 1] * rg[n - 1] : zg[n - 1];
+        if (dinv) zg[n - 1] = zv;
+        s += rg[n - 1] * zv;
     }
     s = block_sum(s, red);
     double tot;
@@ -156,7 +176,7 @@ __global__ void k_pcg_finish(CgState* cg, int nrhs) {
 }
 
 unsigned blocks_for(int64_t n, int max_blocks) {
-    int64_t b = (n + (int64_t)kThreads * 16 - 1) / ((int64_t)kThreads * 16);
+    int64_t b = (n + (int64_t)kThreads * 4 - 1) / ((int64_t)kThreads * 4);
     if (b < 1) b = 1;
     if (b > max_blocks) b = max_blocks;
     return (unsigned)b;
