@@ -10,6 +10,7 @@ enum Epilogue : int32_t {
     EPI_RESID  = 2,   // r = b - (contraction + diag * x), partial r.r
     EPI_MATVEC = 3,   // y = contraction + diag * x
     EPI_RESID_CG = 4, // as EPI_RESID, total ||r||^2 goes to CgState::rho_true (reliable updates)
+    EPI_EIG    = 5,   // y = contraction / (eigenvalue of the element + shift); FP64 COLS only
 };
 
 // One pass contracts a single tensor mode with one factor per Kronecker term.
@@ -41,6 +42,8 @@ struct PassArgs {
                           // (pbuf / pswap of the CG state), else null
     const void* dvec;     // diagonal d (vector element type), may be null
     double sigma2;
+    const double* lam[3]; int64_t lam_n3; double lam_shift;   // EIG: eigenvalues of the modes (lam[2] may be
+                                                              // null), size of mode 3 (or 1)
 
     double* partials; int32_t part_stride;   // per right-hand side
     uint32_t* counters;                       // per right-hand side

@@ -66,10 +66,10 @@ __device__ inline uint32_t xcd_order(uint32_t b, uint32_t T) {
 // Waves per SIMD to leave registers for: as many blocks as the LDS stages allow.
 constexpr int mode_waves(int wm, int wn) { return wm + wn <= 4 ? 4 : (wm + wn <= 5 ? 3 : (wm * wn <= 8 ? 2 : 1)); }
 
-// ROWS or COLS layout; PNEW (ROWS): the vector operand is R + beta X; FULL (COLS): an epilogue with
-// operands, not EPI_STORE; GENERAL: 64-bit indexes and
+// ROWS or COLS layout; PNEW (ROWS): the vector operand is R + beta X; EK (COLS): the kind of epilogue,
+// 0 EPI_STORE, 1 one with vector operands, 2 EPI_EIG; GENERAL: 64-bit indexes and
 // element loads, for inputs of fewer elements than one vector and tiles that span 2 GB.
-template <class P, int WM, int WN, bool ROWS, bool PNEW, bool FULL, bool GENERAL>
+template <class P, int WM, int WN, bool ROWS, bool PNEW, int EK, bool GENERAL>
 __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs a, uint32_t nMt, uint32_t nNt, uint32_t total) {
     using V = typename P::V; using Acc = typename P::Acc; using Vec = typename P::Vec; using VecU = typename P::VecU;
     constexpr int MT = 32 * WM, NT = 32 * WN, VW = P::VW;
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     constexpr int RV = KT / VW;                              // vectors per k-contiguous row
     constexpr int AV = MT * RV / kThreads;                   // vectors per thread and slice
     constexpr int BV = NT * KT / VW / kThreads;
-    constexpr bool F64 = sizeof(V) == 8;
+    constexpr bool F64 = sizeof(V) == 8, FULL = EK == 1;
     __shared__ __attribute__((aligned(16))) V lds[2 * (A_EL + B_EL)];
     __shared__ double red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -397,6 +397,13 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
                     const int e = x * CW + c;
                     const V val = (V)acc[i][j0 + j][e];
                     const bool in = full || (m < Mrows && n + c < Ncols);
+                    if constexpr (EK == 2) {                 // the order of products of k_eig_scale
+                        const uint32_t nc = (uint32_t)(n < Ncols ? n : Ncols - 1), n3 = (uint32_t)a.lam_n3;
+                        double lam = a.lam[0][m < Mrows ? m : Mrows - 1] * a.lam[1][nc / n3];
+                        if (a.lam[2]) lam *= a.lam[2][nc % n3];
+                        out[c] = val / (lam + a.lam_shift);
+                        continue;
+                    }
                     if constexpr (!FULL) {
                         out[c] = val;
                         continue;
@@ -443,13 +450,13 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     }
 }
 
-template <class P, int WM, int WN, bool ROWS, bool PNEW, bool FULL, bool GENERAL>
+template <class P, int WM, int WN, bool ROWS, bool PNEW, int EK, bool GENERAL>
 hipError_t launch_v(const PassArgs& a, hipStream_t s) {
     const int64_t M = ROWS ? a.G : a.nk, N = ROWS ? a.nk : a.B;
     const int64_t nMt = (M + 32 * WM - 1) / (32 * WM), nNt = (N + 32 * WN - 1) / (32 * WN);
     const int64_t total = nMt * nNt * a.nout * (ROWS ? 1 : a.G);
     if (total < 1 || total > 0x7fffffff || (!ROWS && a.G > 0x7fffffff)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_mode<P, WM, WN, ROWS, PNEW, FULL, GENERAL>), dim3((unsigned)total), dim3(kThreads), 0, s, a,
+    hipLaunchKernelGGL((k_mode<P, WM, WN, ROWS, PNEW, EK, GENERAL>), dim3((unsigned)total), dim3(kThreads), 0, s, a,
                        (uint32_t)nMt, (uint32_t)nNt, (uint32_t)total);
     return hipGetLastError();
 }
@@ -462,21 +469,28 @@ bool needs_general(bool rows, const PassArgs& a) {
            (!rows && ((int64_t)P::KT * a.B + 128) * es > 0x7fffffff);
 }
 
+template <class P, int WM, int WN, bool GENERAL>
+hipError_t launch_cols(const PassArgs& a, hipStream_t s) {
+    if (a.epi == EPI_STORE) return launch_v<P, WM, WN, false, false, 0, GENERAL>(a, s);
+    if constexpr (sizeof(typename P::V) == 8)
+        if (a.epi == EPI_EIG) return launch_v<P, WM, WN, false, false, 2, GENERAL>(a, s);
+    if (a.epi == EPI_EIG) return hipErrorInvalidValue;
+    return launch_v<P, WM, WN, false, false, 1, GENERAL>(a, s);
+}
+
 template <class P, int WM, int WN, bool ROWS>
 hipError_t launch_t(const PassArgs& a, hipStream_t s) {
     const bool elem = needs_general<P>(ROWS, a);
     if constexpr (ROWS) {
         if constexpr (WM == 1 && WN == 1)
-            if (elem) return a.pnew ? launch_v<P, 1, 1, true, true, false, true>(a, s)
-                                    : launch_v<P, 1, 1, true, false, false, true>(a, s);
-        return a.pnew ? launch_v<P, WM, WN, true, true, false, false>(a, s)
-                      : launch_v<P, WM, WN, true, false, false, false>(a, s);
+            if (elem) return a.pnew ? launch_v<P, 1, 1, true, true, 0, true>(a, s)
+                                    : launch_v<P, 1, 1, true, false, 0, true>(a, s);
+        return a.pnew ? launch_v<P, WM, WN, true, true, 0, false>(a, s)
+                      : launch_v<P, WM, WN, true, false, 0, false>(a, s);
     } else {
         if constexpr (WM == 1 && WN == 1)
-            if (elem) return a.epi != EPI_STORE ? launch_v<P, 1, 1, false, false, true, true>(a, s)
-                                                : launch_v<P, 1, 1, false, false, false, true>(a, s);
-        return a.epi != EPI_STORE ? launch_v<P, WM, WN, false, false, true, false>(a, s)
-                                  : launch_v<P, WM, WN, false, false, false, false>(a, s);
+            if (elem) return launch_cols<P, 1, 1, true>(a, s);
+        return launch_cols<P, WM, WN, false>(a, s);
     }
 }
 

@@ -44,3 +44,11 @@ def test_scaled_factors():
     s = wl.random_system(rng, (20, 24), sigma2=0.2)
     s.factors = [[s.factors[0][0] * 1e-70, s.factors[0][1] * 1e70]]
     _check([s])
+
+
+@pytest.mark.parametrize("dims", [(31, 3, 11), (32, 5, 7), (33, 1, 31), (2, 33, 33), (5, 31, 4), (33, 32), (3, 65)],
+                         ids=str)
+def test_division_in_the_last_product(dims):
+    """The eigenvalues of two and three modes at the edges of the last product's tiles."""
+    rng = np.random.default_rng(sum(dims) + 1)
+    _check([wl.random_system(rng, dims, sigma2=0.4)], nrhs=3)
