@@ -1714,7 +1714,7 @@ int32_t cola_op_destroy(cola_op_t op) {
     if (op->eig_q) cola_op_destroy(op->eig_q);
     for (hipEvent_t e : op->fused_done)
         if (e) (void)hipEventDestroy(e);
-    void* ptrs[] = {op->fac64, op->fac32, op->facbf, op->diag64, op->diag32, op->grad_buf, op->eig_lam,
+    void* ptrs[] = {op->fac64, op->fac32, op->facbf, op->diag64, op->diag32, op->eig_lam,
                     op->eig_tmp, op->fused_slots, op->slq_buf, op->pc_dinv, op->small_sys};
     for (void* p : ptrs)
         if (p) dev_free(op, p);

@@ -119,8 +119,6 @@ struct cola_op_s {
     cola::Workspace ws;
     cola::Profiler prof;
     std::map<cola::PassKey, cola::TileCfg> tiles;
-    double* grad_buf = nullptr;     // split-K slices of factor gradients that exceed the workspace
-    size_t grad_buf_elems = 0;
     int tiles_version = 0;          // bumped when the tile table changes (invalidates graphs)
     bool graphs_ok = true;          // false after a capture failure: launch directly
     bool use_slab = true;           // fuse modes 2 and 3 of three-mode terms when slabs fit in LDS
