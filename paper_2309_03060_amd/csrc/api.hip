@@ -24,6 +24,7 @@
 #include "op.h"
 #include "resident.h"
 #include "slab.h"
+#include "tiny.h"
 #include "small.h"
 #include "pcg.h"
 #include "slq.h"
@@ -182,6 +183,24 @@ int32_t enqueue_mvm(cola_op_s* op, const SysInfo& s, int prec, int nrhs, const v
     if (s.diag_off >= 0)
         diag = (prec == COLA_PREC_FP64) ? (const void*)(op->diag64 + s.diag_off)
                                         : (const void*)(op->diag32 + s.diag_off);
+    if (tmpl.epi == EPI_MATVEC && (prec == COLA_PREC_FP64 || prec == COLA_PREC_FP32) &&
+        tiny_mvm_supported(s.Fv, s.J, s.dims, nrhs, (int)esz)) {
+        TinyArgs t;
+        t.F = s.Fv;
+        t.J = s.J;
+        t.nrhs = nrhs;
+        for (int k = 0; k < 3; ++k) {
+            t.dims[k] = k < s.Fv ? (int32_t)s.dims[k] : 1;
+            t.K[k] = k < s.Fv ? (const char*)fac + (size_t)s.fac_off[k] * esz : nullptr;
+        }
+        t.X = X;
+        t.Y = Yout;
+        t.dvec = diag;
+        t.sigma2 = s.sigma2;
+        ProfScope ps(prof, "tiny_mvm", st);
+        HIP_TRY(launch_tiny_mvm(prec, t, st));
+        return COLA_OK;
+    }
     if (prec == COLA_PREC_FP64 && op->use_gemm64 && tmpl.epi != EPI_STORE && !tmpl.Ex &&
         gemm64_supported(s.Fv, s.dims) &&
         (tmpl.epi == EPI_MATVEC || gemm64_blocks_per_rhs(s.dims[0], s.dims[1]) <= tmpl.part_stride)) {
