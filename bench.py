@@ -950,6 +950,9 @@ def kernel_class(name):
     m = re.search(r"k_contract<cola::Pol(\w+), \d+, \d+, (true|false)>", name)
     if m:
         return f"contract_{'rows' if m.group(2) == 'true' else 'cols'}_{m.group(1).lower()}"
+    m = re.search(r"k_mode<(?:cola::)?(?:\(anonymous namespace\)::)?Mode(\w+), \d+, \d+, (true|false)", name)
+    if m:
+        return f"contract_{'rows' if m.group(2) == 'true' else 'cols'}_{m.group(1).lower()}"
     m = re.search(r"k_slab23<cola::Slab(\w+)[,>]", name)
     if m:
         return f"slab23_{m.group(1).lower()}"

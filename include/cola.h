@@ -350,7 +350,7 @@ int32_t cola_autotune_import(cola_op_t op, const char* text);
 #define COLA_ENGINE_FUSED_CG 1  /* persistent CG, one cooperative launch per chunk of iterations:
                                    one-term K1 (x) K2 (x) K3 (+ diag) with modes of up to 64, FP32
                                    working precision, no residual history, where it is the faster
-                                   one (64-wide modes; small ones; more than 4 right-hand sides).  With check_every
+                                   one (64-wide modes; small ones; enough right-hand sides).  With check_every
                                    = 0 every chunk (128 iterations with 64-wide modes, else 32) is enqueued up front
                                    (capture-safe); a barrier time-out, which a captured launch
                                    can meet if other work shares the GPU, is then reported
@@ -358,7 +358,7 @@ int32_t cola_autotune_import(cola_op_t op, const char* text);
 #define COLA_ENGINE_GEMM2    2  /* dense-GEMM MVM: BF16, two-mode, modes multiples of 256       */
 #define COLA_ENGINE_GEMM3    3  /* dense-GEMM MVM: FP32 or BF16x3, one-term three-mode, 256-wide
                                    modes                                                     */
-#define COLA_ENGINE_SLAB     4  /* fused mode-2/mode-3 products of three-mode terms, modes <= 64 */
+#define COLA_ENGINE_SLAB     4  /* fused mode-2/mode-3 products of three-mode terms, 64-wide modes */
 #define COLA_ENGINE_RESIDENT 5  /* resident batched CG of many small two-mode systems           */
 #define COLA_ENGINE_SMALL64  6  /* FP64 solves of one-term two-mode systems with modes <= 64: the
                                    whole CG of each (system, RHS) in one workgroup (no precond) */
@@ -374,7 +374,8 @@ int32_t cola_op_set_engine(cola_op_t op, int32_t engine, int32_t enable);
  * epilogue), "update" (x, r update and residual norm), "resident" (batched
  * small systems), "cg_fused" (one launch of the persistent CG: a chunk of
  * iterations for a batch of right-hand sides), "gemm_pack", "gemm_mode3",
- * "gemm_mode2", "gemm_mode1" (the dense-GEMM engines' passes); the same names with "_fp64" for
+ * "gemm_mode2", "gemm_mode1" (the dense-GEMM engines' passes), "tiny_mvm" (whole
+ * products of the smallest operators, FP64 and FP32); the same names with "_fp64" for
  * launches in FP64 (plain FP64 solves and the FP64 residuals of mixed precision).  enable != 0
  * starts collecting (and clears totals). */
 int32_t cola_profile_enable(cola_op_t op, int32_t enable);

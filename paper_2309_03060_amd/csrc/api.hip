@@ -404,15 +404,13 @@ int32_t enqueue_mvm(cola_op_s* op, const SysInfo& s, int prec, int nrhs, const v
     int64_t in_tstride = 0;
     int buf = 0;
     int kstart = s.Fv - 1;
-    if (s.Fv == 3 && op->use_slab && slab_supported(prec, s.dims[1], s.dims[2])) {
+    if (s.Fv == 3 && op->use_slab && slab_supported(prec, s.dims[1], s.dims[2], nrhs * s.dims[0])) {
         // modes 3 and 2 of every term in one pass over n2 x n3 slabs
         const size_t fb = (prec == COLA_PREC_FP64) ? 8 : 4;
         SlabArgs sa;
         std::memset(&sa, 0, sizeof(sa));
         sa.nslabs = (int64_t)nrhs * s.dims[0];
         sa.a_per_rhs = s.dims[0];
-        sa.n2 = (int32_t)s.dims[1];
-        sa.n3 = (int32_t)s.dims[2];
         sa.nterms = s.J;
         sa.pnew = Rpnew != nullptr;
         sa.X = X;
@@ -657,7 +655,7 @@ bool capturing(hipStream_t st) {
 bool fused_eligible(const cola_op_s* op, const SysInfo& s, int prec, int check_every, int nrhs) {
     // the persistent kernel runs its own vector update, which records no residual history
     return op->use_fused && check_every >= 0 && op->fused_max_blocks != 0 && prec == op->prec && !op->ws.rh.data &&
-           fused_cg_supported(prec, s.Fv, s.J, s.dims) && fused_cg_pays(s.dims, nrhs);
+           fused_cg_supported(prec, s.Fv, s.J, s.dims) && fused_cg_pays(s.dims, nrhs, op->fused_max_blocks);
 }
 
 // CG iterations of a one-term three-mode FP32 operator with modes of up to 64:

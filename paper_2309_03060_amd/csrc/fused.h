@@ -30,7 +30,7 @@ struct FusedCgArgs {
 bool fused_cg_supported(int prec, int Fv, int J, const int64_t* dims);
 
 // Whether the engine is the faster one for this shape (64-wide modes always).
-bool fused_cg_pays(const int64_t* dims, int nrhs);
+bool fused_cg_pays(const int64_t* dims, int nrhs, int max_blocks);
 
 // Largest number of fused-CG blocks that can be resident at once on the
 // current device (0 when cooperative launches are unavailable).

@@ -580,17 +580,6 @@ namespace {
 int64_t units_of(const int64_t* dims) { return std::max(dims[0], (dims[1] * dims[2] + D - 1) / D); }
 }  // namespace
 
-// An iteration is three group barriers, whose cost grows with the group, and hardly depends on the
-// number of right-hand sides until the chip is full; three kernels cost about 23 us an iteration
-// and then by volume.  Measured, fused against separate kernels, us an iteration: 16^3, groups of 4:
-// 18 / 23 at 1 right-hand side, 19 / 27 at 32; 32^3, groups of 8: 22.5 / 23 at 1, 23 / 30 at 16;
-// 50^3, groups of 16: 32.5 / 28 at 1, 32 / 31 at 4, 36.5 / 58 at 16; 60 x 20 x 20, groups of 16:
-// 24.5 / 24 at 4, 26 / 35 at 16; 48 x 40 x 56 at 16: 31 / 54.
-bool fused_cg_pays(const int64_t* dims, int nrhs) {
-    const bool full = dims[0] == D && dims[1] == D && dims[2] == D;
-    return full || units_of(dims) <= 32 || nrhs > 4;
-}
-
 // The slabs (n1) and strips (n2 n3 / 64) of a right-hand side, one to a quad if all right-hand sides
 // then fit the chip at once, else two; 4 quads to a block.
 FusedShape fused_cg_shape(const int64_t* dims, int nrhs, int max_blocks) {
@@ -600,6 +589,26 @@ FusedShape fused_cg_shape(const int64_t* dims, int nrhs, int max_blocks) {
     while (4 * bpr < units) bpr *= 2;                      // 4, 8 or 16 blocks
     if ((int64_t)nrhs * bpr <= max_blocks || bpr == 4) return FusedShape{bpr, 1};
     return FusedShape{bpr / 2, 2};
+}
+
+// Both engines' iteration in us, from a sweep of twelve shapes at 5 .. 32 right-hand sides.  Fused: three
+// group barriers, whose cost grows with the group, and the group's volume; 1.6 times that with two slabs
+// to a quad; once per launch the right-hand sides need.  Separate kernels: about 18.5 us of launches
+// until the volume takes over.  Measured, fused / separate: groups of 4: 16^3 at 5 16.6 / 18.6; of 8:
+// 20^3 at 5 18.9 / 19.1, 32^3 at 8 20.8 / 18.6, at 32 21.6 / 29.0; of 16: 48 x 40 x 56 at 5 28.0 / 27.4, at 8
+// 27.9 / 33.1, 60 x 20 x 20 at 16 23.8 / 23.0, 63 x 61 x 59 at 8 37.4 / 41.4, 50^3 at 32 59 / 74.
+// 64-wide modes have a variant of their own that is always ahead.
+bool fused_cg_pays(const int64_t* dims, int nrhs, int max_blocks) {
+    if (dims[0] == D && dims[1] == D && dims[2] == D) return true;
+    if (max_blocks < 8) max_blocks = 256;                  // not yet queried
+    const FusedShape f = fused_cg_shape(dims, nrhs, max_blocks);
+    const double n = (double)(dims[0] * dims[1] * dims[2]);
+    const int group = f.bpr * f.spq;                       // 4, 8 or 16 quads' blocks
+    const int at_once = max_blocks / f.bpr;
+    double fused = group <= 4 ? 16.5 : (group == 8 ? 17.5 + 1.1e-4 * n : 22.5 + 7e-5 * n);
+    if (f.spq == 2) fused *= 1.6;
+    fused *= (double)((nrhs + at_once - 1) / at_once);
+    return fused < std::max(18.5, 16.0 + 18e-6 * n * nrhs);
 }
 
 namespace {

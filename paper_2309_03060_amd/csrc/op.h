@@ -121,7 +121,7 @@ struct cola_op_s {
     std::map<cola::PassKey, cola::TileCfg> tiles;
     int tiles_version = 0;          // bumped when the tile table changes (invalidates graphs)
     bool graphs_ok = true;          // false after a capture failure: launch directly
-    bool use_slab = true;           // fuse modes 2 and 3 of three-mode terms when slabs fit in LDS
+    bool use_slab = true;           // fuse modes 2 and 3 of three-mode terms in 64 x 64 slabs
     bool use_gemm2 = true;          // BF16 two-mode operators with large modes: dense-GEMM MVM
     bool use_gemm3 = true;          // FP32 one-term three-mode operators with 256-wide modes: dense-GEMM MVM
     bool use_gemm64 = true;         // FP64 passes of two-mode operators with modes multiples of 256: dense FP64 GEMMs

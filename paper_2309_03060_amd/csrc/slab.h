@@ -5,9 +5,8 @@
 namespace cola {
 
 struct SlabArgs {
-    int64_t nslabs;        // nrhs * n1 slabs of n2 x n3
+    int64_t nslabs;        // nrhs * n1 slabs of 64 x 64
     int64_t a_per_rhs;     // slabs per right-hand side (n1)
-    int32_t n2, n3;
     int32_t nterms;        // one output per term (grid dimension)
     int32_t pnew;          // slab = R + beta * X (first pass of a CG iteration)
     const void* X;
@@ -18,7 +17,8 @@ struct SlabArgs {
     CgState* cg;                                // beta of the direction update
 };
 
-bool slab_supported(int prec, int64_t n2, int64_t n3);
+// Whether the fused product takes modes n2 x n3 with this many slabs in all.
+bool slab_supported(int prec, int64_t n2, int64_t n3, int64_t nslabs);
 hipError_t launch_slab23(int prec, const SlabArgs& a, hipStream_t s);
 
 }  // namespace cola

@@ -3,8 +3,7 @@
 // For a term K1 (x) K2 (x) K3 and X = x.reshape(n1, n2, n3), the mode-2 and
 // mode-3 products act on each n2 x n3 slab X[i1] independently:
 // T[i1] = K2 X[i1] K3^T (the per-mode evaluation behind the Kronecker MVM
-// cost of Table 2).  When a slab fits in LDS (n2, n3 <= 64) both products
-// are done there: the slab is read once, the intermediate product never
+// cost of Table 2).  For slabs of 64 x 64 both products are done in LDS: the slab is read once, the intermediate product never
 // leaves the CU, and T is written once.  Blocks are persistent over a range
 // of slabs so the two factors are staged in LDS once per block, and the next
 // slab's loads are issued while the current one is being multiplied.
@@ -41,10 +40,10 @@ __device__ inline void sstore4(double* p, const double* v) {
     *(d2*)(p + 2) = d2{v[2], v[3]};
 }
 
-// FULL: 64 x 64 slabs (16-byte loads); PNEW: the slab is the CG direction
-// r + beta p.  Both are template parameters so the prefetch below is
-// straight-line code the compiler can leave in flight across the products.
-template <class S, bool FULL, bool PNEW>
+// PNEW: the slab is the CG direction r + beta p (a template parameter, so the
+// prefetch below is straight-line code the compiler can leave in flight
+// across the products).
+template <class S, bool PNEW>
 __global__ __launch_bounds__(kThreads) void k_slab23(SlabArgs a) {
     using V = typename S::V;
     using Acc = typename S::Acc;
@@ -55,20 +54,17 @@ __global__ __launch_bounds__(kThreads) void k_slab23(SlabArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int lr = lane & 15, lq = lane >> 4;
-    const int n2 = a.n2, n3 = a.n3;
-    const int64_t slab = (int64_t)n2 * n3;
     const int term = blockIdx.y;
     const V* K2 = (const V*)a.K2 + (int64_t)term * a.k2_tstride;
     const V* K3 = (const V*)a.K3 + (int64_t)term * a.k3_tstride;
     V* Yt = (V*)a.Y + (int64_t)term * a.y_tstride;
     const V* X = (const V*)a.X;
     const V* R = (const V*)a.R;
-    constexpr bool full = FULL;
 
     for (int e = tid; e < D * D; e += kThreads) {
         const int r = e / D, c = e % D;
-        K2s[r * KP + c] = (r < n2 && c < n2) ? K2[r * n2 + c] : (V)0;
-        K3s[r * KP + c] = (r < n3 && c < n3) ? K3[r * n3 + c] : (V)0;
+        K2s[r * KP + c] = K2[e];
+        K3s[r * KP + c] = K3[e];
     }
 
     // The first product U = P K3^T is done per wave on a 16-row strip of the
@@ -79,26 +75,12 @@ __global__ __launch_bounds__(kThreads) void k_slab23(SlabArgs a) {
     const int arow = 16 * wave + lr;             // slab row of this lane's A values
     V pv[16], rv[16];
     auto load_strip = [&](int64_t sl) {
-        const int64_t base = sl * slab;
-        if constexpr (FULL) {
+        const int64_t base = sl * D * D;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t off = base + arow * D + 16 * u + 4 * lq;
-                sload4(X + off, pv + 4 * u);
-                if constexpr (PNEW) sload4(R + off, rv + 4 * u);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int col = 16 * u + 4 * lq + c;
-                    const bool ok = arow < n2 && col < n3;
-                    const int64_t off = base + (ok ? arow * n3 + col : 0);
-                    pv[4 * u + c] = X[off];
-                    if constexpr (PNEW) rv[4 * u + c] = R[off];
-                    if (!ok) { pv[4 * u + c] = (V)0; if constexpr (PNEW) rv[4 * u + c] = (V)0; }
-                }
+        for (int u = 0; u < 4; ++u) {
+            const int64_t off = base + arow * D + 16 * u + 4 * lq;
+            sload4(X + off, pv + 4 * u);
+            if constexpr (PNEW) sload4(R + off, rv + 4 * u);
         }
     };
 
@@ -198,17 +180,13 @@ __global__ __launch_bounds__(kThreads) void k_slab23(SlabArgs a) {
                     Ut[row * UP + col] = (V)acc[i][j][v];
                 }
         __syncthreads();
-        const int64_t base = sl * slab;
-        if (full) {
-            for (int e = tid; e < D * D / 4; e += kThreads) {
-                const int r = e / (D / 4), c = (e % (D / 4)) * 4;
-                V v[4];
+        const int64_t base = sl * D * D;
+        for (int e = tid; e < D * D / 4; e += kThreads) {
+            const int r = e / (D / 4), c = (e % (D / 4)) * 4;
+            V v[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = Ut[r * UP + c + q];
-                sstore4(Yt + base + r * D + c, v);
-            }
-        } else {
-            for (int e = tid; e < slab; e += kThreads) Yt[base + e] = Ut[(e / n3) * UP + (e % n3)];
+            for (int q = 0; q < 4; ++q) v[q] = Ut[r * UP + c + q];
+            sstore4(Yt + base + r * D + c, v);
         }
         __syncthreads();                           // T read out of U before the next slab writes U
         sl = nx;
@@ -217,27 +195,30 @@ __global__ __launch_bounds__(kThreads) void k_slab23(SlabArgs a) {
     }
 }
 
-bool slab_supported(int prec, int64_t n2, int64_t n3) {
-    return (prec == COLA_PREC_FP32 || prec == COLA_PREC_FP64) && n2 >= 1 && n3 >= 1 && n2 <= 64 && n3 <= 64;
+// 64 x 64 slabs only: smaller ones were padded to 64 x 64 products, and one pass per mode is faster at
+// every count (whole products, one term, slab / modes: 16^3 x 64 right-hand sides FP64 31.7 / 11.7 us,
+// 32^3 x 64 FP32 40.0 / 20.0, 48 x 40 x 56 x 8 FP64 20.3 / 17.0, 100 x 60 x 64 x 16 FP32 71.3 / 61.3).
+// At 64 x 64: FP64 64 slabs 17.1 / 13.4, 1024 60.9 / 56.5, 4096 198 / 217; FP32 64 slabs 12.5 / 10.8, 256
+// 18.4 / 18.3, 4096 98.9 / 106.8.
+bool slab_supported(int prec, int64_t n2, int64_t n3, int64_t nslabs) {
+    if (n2 != 64 || n3 != 64) return false;
+    return (prec == COLA_PREC_FP32 && nslabs >= 128) || (prec == COLA_PREC_FP64 && nslabs >= 2048);
 }
 
 hipError_t launch_slab23(int prec, const SlabArgs& a, hipStream_t s) {
     const int64_t cap = (prec == COLA_PREC_FP64) ? 256 : 768;   // 1 (FP64) or 3 (FP32) blocks per CU
     const unsigned gx = (unsigned)(a.nslabs < cap ? a.nslabs : cap);
     dim3 grid(gx, (unsigned)a.nterms);
-    const bool full = a.n2 == 64 && a.n3 == 64;
     const bool pn = a.pnew != 0;
-#define COLA_SLAB_LAUNCH(S)                                                                              \
-    do {                                                                                                 \
-        if (full && pn) hipLaunchKernelGGL((k_slab23<S, true, true>), grid, dim3(kThreads), 0, s, a);    \
-        else if (full) hipLaunchKernelGGL((k_slab23<S, true, false>), grid, dim3(kThreads), 0, s, a);    \
-        else if (pn) hipLaunchKernelGGL((k_slab23<S, false, true>), grid, dim3(kThreads), 0, s, a);      \
-        else hipLaunchKernelGGL((k_slab23<S, false, false>), grid, dim3(kThreads), 0, s, a);             \
-    } while (0)
-    if (prec == COLA_PREC_FP32) COLA_SLAB_LAUNCH(SlabF32);
-    else if (prec == COLA_PREC_FP64) COLA_SLAB_LAUNCH(SlabF64);
-    else return hipErrorInvalidValue;
-#undef COLA_SLAB_LAUNCH
+    if (prec == COLA_PREC_FP32) {
+        if (pn) hipLaunchKernelGGL((k_slab23<SlabF32, true>), grid, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL((k_slab23<SlabF32, false>), grid, dim3(kThreads), 0, s, a);
+    } else if (prec == COLA_PREC_FP64) {
+        if (pn) hipLaunchKernelGGL((k_slab23<SlabF64, true>), grid, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL((k_slab23<SlabF64, false>), grid, dim3(kThreads), 0, s, a);
+    } else {
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
