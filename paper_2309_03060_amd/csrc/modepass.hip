@@ -18,7 +18,7 @@
 // where a row was not 16-byte aligned and the epilogue through LDS, and now:
 // 97 x 101 x 89, 4 right-hand sides, FP32: last / middle / first mode 29 / 45 / 47
 // -> 15 / 22 / 23 us; 91 x 75 x 61, 4 right-hand sides, FP64 CG: 30 / 33 / 78 ->
-// 12 / 14 / 25 us; 200 x 180, 16 right-hand sides, FP64 CG: 19 / 54 -> 10 / 16 us.
+// 12 / 13 / 20 us; 200 x 180, 16 right-hand sides, FP64 CG: 19 / 54 -> 10 / 13 us.
 #include "modepass.h"
 
 #include <algorithm>

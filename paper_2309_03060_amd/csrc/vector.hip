@@ -418,8 +418,8 @@ static inline unsigned grid_for(int64_t n, int64_t per_block, int64_t cap) {
 
 int vec_blocks_per_rhs(int64_t n) {
     // Up to 128 blocks of four elements a thread, sixteen a thread beyond that, at most 512 blocks.
-    // Small vectors are bound by the chain load -> sum -> arrival, so they spread wide: the updates of
-    // 28k x 24 right-hand sides took 12.0 us with sixteen elements a thread and 4.7 with four.  More
+    // Small vectors are bound by the chain load -> sum -> arrival, so they spread wide: the preconditioned
+    // update of 19650 x 8 right-hand sides took 12.0 us with sixteen elements a thread and 4.7 with four.  More
     // blocks cost arrivals on one counter: 416k x 4 in FP64 17.6 us at 102 blocks, 16.3 at 128, 18.5 at 406.
     const int64_t wide = grid_for(n, (int64_t)kThreads * 4, 128), deep = grid_for(n, (int64_t)kThreads * 16, 512);
     return (int)(wide > deep ? wide : deep);
