@@ -24,6 +24,8 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "modeslice.h"
+
 namespace cola {
 namespace {
 
@@ -77,9 +79,6 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     constexpr int KP = KT + VW;                              // pitch of a k-contiguous row: 4 (mod 64) banks
     constexpr int NTP = NT + P::NPAD;                        // pitch of a COLS panel row
     constexpr int A_EL = MT * KP, B_EL = ROWS ? NT * KP : KT * NTP;
-    constexpr int RV = KT / VW;                              // vectors per k-contiguous row
-    constexpr int AV = MT * RV / kThreads;                   // vectors per thread and slice
-    constexpr int BV = NT * KT / VW / kThreads;
     constexpr bool F64 = sizeof(V) == 8, FULL = EK == 1;
     __shared__ __attribute__((aligned(16))) V lds[2 * (A_EL + B_EL)];
     __shared__ double red[4];
@@ -114,56 +113,35 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     }
     const int64_t Mrows = ROWS ? a.G : nk;                   // rows and columns of the output matrix
     const int64_t Ncols = ROWS ? nk : a.B;
-    // This thread's vectors, as 32-bit byte offsets from a uniform base that moves from slice to slice.
-    // Nothing branches between a slice's loads (a branch would make the compiler wait for the loads in
-    // flight).  Only the last slice can leave its buffers; it has offsets of its own, clamped: rows of a
-    // panel beyond nk repeat row nk - 1, and a vector past the end of the input is read early.  What a
-    // clamp moved, and what lies beyond nk, is put right on the way to LDS.  Rows of the output tile
-    // beyond the matrix repeat its last row and columns beyond it hold other elements: neither is
-    // stored.  Factor vectors may run past the end of their matrix by part of a slice (the factor
-    // buffers are padded by a slice's 128 bytes).
+    // This thread's vectors, as 32-bit byte offsets from a uniform base that moves from slice to slice
+    // (modeslice.h says where they lie and why they stay inside the input).  Nothing branches between a
+    // slice's loads (a branch would make the compiler wait for the loads in flight).  What the clamps of
+    // the last slice moved, and what lies beyond nk, is put right on the way to LDS.
     constexpr int ES = sizeof(V);
-    const int k_last = (ns - 1) * KT;                        // k0 of a term's last slice
-    const int arow0 = tid / RV, akc = (tid % RV) * VW;       // k-contiguous vector q: row arow0 + q (256 / RV)
-    constexpr int RQ = kThreads / RV;
-    constexpr int PR = NT / VW, PQ = kThreads / PR;          // COLS: vectors per panel row, rows per step of q
-    const int bk0 = tid / PR, bn = (tid % PR) * VW;
-    // the input from the tile's base (ROWS: row m0, COLS: column n0 of batch g): its last vector
-    const int64_t x_base = ROWS ? m0 * nk : g * nk * a.B + n0;
-    const int64_t x_end = (ROWS ? a.G * nk : a.G * nk * a.B) - (GENERAL ? 1 : VW) - x_base;
-    const int64_t xstep = ROWS ? KT : (int64_t)KT * a.B;
-    const int64_t x_end_last = x_end - (int64_t)(ns - 1) * xstep;        // from the base of the last slice
-    auto row_at = [&](int q, int64_t first, int64_t rows) {              // of tile row arow0 + q RQ, clamped
-        const int64_t m = first + arow0 + q * RQ;
-        return (m < rows ? m : rows - 1) - first;
-    };
-    // element offsets of vector q of the input: in a slice, and in the last one before its clamp to the end
-    auto in_off = [&](int q) -> int64_t {
-        return ROWS ? row_at(q, m0, Mrows) * nk + akc : (int64_t)(bk0 + q * PQ) * a.B + bn;
-    };
-    auto in_off_last = [&](int q) -> int64_t {
-        if constexpr (ROWS) return in_off(q);
-        const int k = bk0 + q * PQ;
-        return (int64_t)(k_last + k < nk ? k : nk - 1 - k_last) * a.B + bn;
-    };
-    constexpr int XV = ROWS ? AV : BV, FV = ROWS ? BV : AV;  // vectors of the input and of the factor
+    using Slices = ModeSlices<VW, KT, WM, WN, ROWS>;
+    const Slices sl{nk, a.B, a.G, m0, n0, g};
+    constexpr int AV = Slices::AV, BV = Slices::BV, XV = Slices::XV, FV = Slices::FV;
+    constexpr int RQ = Slices::RQ, PQ = Slices::PQ;
+    const int k_last = sl.k_last();                          // k0 of a term's last slice
+    const int arow0 = sl.row(tid, 0), akc = sl.row_k(tid);   // k-contiguous vector q: row arow0 + q RQ
+    const int bk0 = sl.panel_k(tid, 0), bn = sl.panel_col(tid);          // panel vector q: k bk0 + q PQ
+    const int64_t x_end = sl.x_end(GENERAL ? 1 : VW), x_end_last = sl.x_end_last(GENERAL ? 1 : VW);
+    const int64_t xstep = sl.x_step();
     uint32_t xoff[XV], xlast[XV], foff[FV];
 #pragma unroll
     for (int q = 0; q < XV; ++q) {
-        const int64_t l = in_off_last(q);
-        xoff[q] = (uint32_t)(in_off(q) * ES);
-        xlast[q] = (uint32_t)(((l < x_end_last ? l : x_end_last) + VW) * ES);   // from VW elements before it
+        xoff[q] = (uint32_t)(sl.x_at(tid, q) * ES);
+        xlast[q] = (uint32_t)((sl.x_last(tid, q) + VW) * ES);            // from VW elements before it
     }
 #pragma unroll
-    for (int q = 0; q < FV; ++q)
-        foff[q] = (uint32_t)((row_at(q, ROWS ? n0 : m0, nk) * nk + akc) * ES);
+    for (int q = 0; q < FV; ++q) foff[q] = (uint32_t)(sl.f_at(tid, q) * ES);
     double beta[PNEW ? AV : 1];
     if constexpr (PNEW) {
 #pragma unroll
-        for (int q = 0; q < AV; ++q) beta[q] = a.cg[rhs_of(a, m0 + row_at(q, m0, Mrows))].beta;
+        for (int q = 0; q < AV; ++q) beta[q] = a.cg[rhs_of(a, m0 + sl.row_at(sl.row(tid, q), m0, a.G))].beta;
     }
-    // whether some vector of the last slice was read early
-    const bool tail = x_end_last < (ROWS ? (int64_t)(MT - 1) * nk + KT : (int64_t)(nk - 1 - k_last) * a.B + NT);
+    const bool tail = sl.x_clamped();                        // some vector of the last slice was read early
+    const int idle = (int)(-sl.x_idle() * ES);               // bytes before the last slice's base
 
     struct Slice { Vec a[AV], r[PNEW ? AV : 1], b[BV]; };
     auto ldv = [&](const char* base, uint32_t off) -> Vec { return *(const VecU*)(base + off); };
@@ -177,8 +155,8 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     // the slice the next load takes: bases of its operands, k0
     const int64_t t0 = a.nsum > 1 ? 0 : tout;
     const char* Fl = (const char*)((const V*)a.K + t0 * a.k_tstride + (ROWS ? n0 : m0) * nk);
-    const char* Xl = (const char*)((const V*)a.X + t0 * a.x_tstride + x_base);
-    const char* Rl = (const char*)((const V*)a.R + t0 * a.x_tstride + x_base);
+    const char* Xl = (const char*)((const V*)a.X + t0 * a.x_tstride + sl.x_base());
+    const char* Rl = (const char*)((const V*)a.R + t0 * a.x_tstride + sl.x_base());
     int kl = 0, left = steps;
     auto load_slice = [&](Slice& v) {
         // past the last slice every lane loads one address (nothing uses it)
@@ -190,15 +168,15 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
             const int64_t end = x_end - (int64_t)(kl / KT) * xstep;
 #pragma unroll
             for (int q = 0; q < XV; ++q) {
-                const int64_t i = left > 0 ? (last ? in_off_last(q) : in_off(q)) : 0;
+                const int64_t i = left > 0 ? (last ? sl.x_last_wanted(tid, q) : sl.x_at(tid, q)) : 0;
                 vx[q] = ld_elem((const V*)Xl, i, end);
                 if constexpr (PNEW) v.r[q] = ld_elem((const V*)Rl, i, end);
             }
 #pragma unroll
             for (int q = 0; q < FV; ++q)
-                vf[q] = *(const VecU*)((const V*)Fl + (left > 0 ? row_at(q, ROWS ? n0 : m0, nk) * nk + akc : 0));
+                vf[q] = *(const VecU*)((const V*)Fl + (left > 0 ? sl.f_at(tid, q) : 0));
         } else {
-            const int back = last && left > 0 ? VW * ES : 0;
+            const int back = left > 0 ? (last ? VW * ES : 0) : idle;
 #pragma unroll
             for (int q = 0; q < XV; ++q) {
                 const uint32_t o = (last ? xlast[q] : xoff[q]) & keep;
@@ -240,7 +218,7 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
         if (!GENERAL && tail && k0 == k_last) {
 #pragma unroll
             for (int q = 0; q < XV; ++q) {
-                const int64_t sh = in_off_last(q) - x_end_last;
+                const int64_t sh = sl.x_last_wanted(tid, q) - x_end_last;
                 if constexpr (ROWS) unshift(v.a[q], sh);
                 else unshift(v.b[q], sh);
                 if constexpr (PNEW) unshift(v.r[q], sh);
@@ -461,12 +439,9 @@ hipError_t launch_v(const PassArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Fewer elements than one vector, or 128 rows (a slice of panel rows) that span 2 GB.
 template <class P>
 bool needs_general(bool rows, const PassArgs& a) {
-    const int64_t es = sizeof(typename P::V), span = ((int64_t)128 * a.nk + 128) * es;
-    return (rows ? a.G * a.nk : a.G * a.nk * a.B) < P::VW || span > 0x7fffffff ||
-           (!rows && ((int64_t)P::KT * a.B + 128) * es > 0x7fffffff);
+    return mode_needs_general<P::VW, P::KT>(rows, a.nk, a.B, a.G, sizeof(typename P::V));
 }
 
 template <class P, int WM, int WN, bool GENERAL>
