@@ -28,7 +28,7 @@ struct JacobiItem {
 struct JacobiState {
     int32_t done;        // a sweep found every pair within the tolerance
     int32_t rotated[2];  // whether the last sweep, and the one before, rotated anything (by sweep mod 2)
-    int32_t pad;
+    int32_t exponent;    // the factor is decomposed as A 2^-exponent (entries of at most 1)
 };
 
 // Largest factor a workgroup holds in LDS (n * n doubles of 160 KB, with room for the rest).

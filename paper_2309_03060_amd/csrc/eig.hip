@@ -10,6 +10,7 @@
 #include "eig.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <vector>
 
@@ -197,7 +198,7 @@ __device__ inline void jacobi_row(double* v, double* q, int n, int i, const doub
 __global__ __launch_bounds__(kJacThreads) void k_jacobi_round(const JacobiItem* items, JacobiState* state, int nitems,
                                                               int sweep, int last, double tol) {
     __shared__ double U[kJacobiLds * (kJacobiLds + kJacPad)];
-    __shared__ int s_rotated;
+    __shared__ int s_rotated, s_exponent;
     const int b = blockIdx.x, tid = threadIdx.x, now = sweep & 1;
     if (b >= nitems) {
         const int f = (b - nitems) % nitems, i = (b - nitems) / nitems * (kJacThreads / 64) + (tid >> 6);
@@ -215,9 +216,27 @@ __global__ __launch_bounds__(kJacThreads) void k_jacobi_round(const JacobiItem* 
     }
     const JacobiItem it = items[b];
     const int n = it.n, ld = n + kJacPad;
-    const double* src = sweep == 0 ? it.A : it.u;
-    if (tid == 0) s_rotated = 0;
-    for (int e = tid; e < n * n; e += kJacThreads) U[(e / n) * ld + e % n] = src[e];
+    if (tid == 0) {
+        s_rotated = 0;
+        s_exponent = INT_MIN;
+    }
+    __syncthreads();
+    if (sweep == 0) {
+        // Scaled by a power of two (exactly) to entries of at most 1: unscaled, the squares of columns
+        // beyond 1e77 overflowed, no pair looked worth a rotation and A's own basis was returned.
+        int top = INT_MIN;
+        for (int e = tid; e < n * n; e += kJacThreads) {
+            const double v = it.A[e];
+            if (v != 0.0 && finite_d(v)) top = max(top, __builtin_amdgcn_frexp_exp(v));
+        }
+        if (top != INT_MIN) atomicMax(&s_exponent, top);
+        __syncthreads();
+        const int ex = s_exponent == INT_MIN ? 0 : s_exponent;
+        for (int e = tid; e < n * n; e += kJacThreads) U[(e / n) * ld + e % n] = ldexp(it.A[e], -ex);
+        if (tid == 0) st.exponent = ex;
+    } else {
+        for (int e = tid; e < n * n; e += kJacThreads) U[(e / n) * ld + e % n] = it.u[e];
+    }
     __syncthreads();
     if (jacobi_sweep_n(U, n, it.rot + now * jacobi_rotations(n), tol)) s_rotated = 1;
     __syncthreads();
@@ -228,8 +247,8 @@ __global__ __launch_bounds__(kJacThreads) void k_jacobi_round(const JacobiItem* 
     }
 }
 
-// Q^T and the eigenvalues of every factor: lam_j = v_j . u_j, one wave a column.
-__global__ __launch_bounds__(kThreads) void k_jacobi_finish(const JacobiItem* items) {
+// Q^T and the eigenvalues of every factor: lam_j = v_j . u_j (scaled back), one wave a column.
+__global__ __launch_bounds__(kThreads) void k_jacobi_finish(const JacobiItem* items, const JacobiState* state) {
     const JacobiItem it = items[blockIdx.y];
     const int n = it.n, lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (j >= n) return;
@@ -240,7 +259,7 @@ __global__ __launch_bounds__(kThreads) void k_jacobi_finish(const JacobiItem* it
         s = __builtin_fma(it.u[(int64_t)j * n + i], v, s);
     }
     s = wave_sum(s);
-    if (lane == 0) it.lam[j] = s;
+    if (lane == 0) it.lam[j] = ldexp(s, state[blockIdx.y].exponent);
 }
 
 // lam_j = v_j . u_j = v_j^T A v_j (the Rayleigh quotient of the converged column).
@@ -330,7 +349,7 @@ int32_t jacobi_eig_batch(const JacobiItem* items, JacobiState* state, int nitems
         }
     }
     const dim3 rows((unsigned)((nmax + 3) / 4), (unsigned)nitems);
-    hipLaunchKernelGGL(k_jacobi_finish, rows, dim3(kThreads), 0, s, items);
+    hipLaunchKernelGGL(k_jacobi_finish, rows, dim3(kThreads), 0, s, items, state);
     return hipGetLastError() == hipSuccess ? COLA_OK : COLA_ERR_HIP;
 }
 
