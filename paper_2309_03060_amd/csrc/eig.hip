@@ -156,10 +156,18 @@ __device__ inline bool jacobi_sweep_n(double* U, int n, double2* rot, double tol
     }
 }
 
+// What the lanes of a wave wrote to LDS before is what they read after it.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Row i of Q: the rotations of one sweep in order, one wave (v: its row in LDS).
 __device__ inline void jacobi_row(double* v, double* q, int n, int i, const double2* rot, bool first) {
     const int lane = threadIdx.x & 63;
     for (int j = lane; j < n; j += 64) v[j] = first ? (j == i ? 1.0 : 0.0) : q[(int64_t)i * n + j];
+    wave_sync();
     const int m = n + (n & 1), np = m / 2;
     constexpr int NK = (kJacobiLds / 2 + 63) / 64;          // pairs per lane
     double2 next[NK];
@@ -183,7 +191,7 @@ __device__ inline void jacobi_row(double* v, double* q, int n, int i, const doub
             v[p] = cs[u].x * x - cs[u].y * y;
             v[q2] = cs[u].y * x + cs[u].x * y;
         }
-        __builtin_amdgcn_wave_barrier();                    // the wave's LDS accesses stay in step order
+        wave_sync();                                        // the next step's pairs hold other lanes' columns
     }
     for (int j = lane; j < n; j += 64) q[(int64_t)i * n + j] = v[j];
 }
