@@ -1,0 +1,27 @@
+"""Which FP32 three-mode solves the persistent CG takes: without host checks only 64-wide modes, so that
+the other shapes' captured solves cannot meet a group barrier.
+"""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import kron
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims,every,fused", [((48, 40, 56), 0, False), ((16, 16, 16), 0, False), ((64, 64, 64), 0, True),
+                                              ((48, 40, 56), 32, True)], ids=str)
+def test_route_by_host_checks(dims, every, fused):
+    from gpu_util import infos, make_op, pack, unpack
+    rng = np.random.default_rng(sum(dims))
+    s = wl.System(factors=[[wl.wishart_factor(rng, m, shift=0.3) for m in dims]], sigma2=0.2, diag=None)
+    B = rng.standard_normal((8, s.n))
+    op = make_op([s], prec="fp32")
+    op.profile_enable(True)
+    X, info = op.solve(pack([B]), 8, tol=1e-6, max_iters=256, inner_tol=0.1, check_every=every)
+    ran, separate = op.profile_read("cg_fused")[1] > 0, op.profile_read("contract_last")[1] > 0
+    assert (ran, separate) == (fused, not fused)
+    rr = kron.relres(s.factors, unpack(X, [s], 8)[0], B, s.sigma2)
+    assert all(i["status"] == 0 for i in infos(info, 8)) and np.all(rr <= 1e-6), rr
+    op.close()
