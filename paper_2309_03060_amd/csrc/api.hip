@@ -661,6 +661,10 @@ bool fused_eligible(const cola_op_s* op, const SysInfo& s, int prec, int check_e
            fused_cg_supported(prec, s.Fv, s.J, s.dims) && fused_cg_pays(s.dims, nrhs, op->fused_max_blocks);
 }
 
+// A group of the fused CG never met (other work held the CUs its last blocks needed for seconds): its
+// vectors are void.  Never leaves solve_system.
+constexpr int32_t kFusedTimedOut = -1000;
+
 // CG iterations of a one-term three-mode FP32 operator with modes of up to 64:
 // every chunk of check_every iterations is one cooperative launch per batch of
 // right-hand sides (then the reliable-update tail), with the host reading the
@@ -695,6 +699,7 @@ int32_t run_cg_fused(cola_op_s* op, const SysInfo& s, int nrhs, float* x, float*
     a.slots = op->fused_slots;
     a.err = (uint32_t*)(op->fused_slots + 3 * (size_t)op->fused_max_blocks);
     a.cnt = w.cnt;
+    a.spin_limit = op->fused_spin_limit;
     float* t = (float*)w.inter[0];
     int last = -1;
     for (int c = 0; c < nchunks; ++c) {
@@ -739,9 +744,10 @@ int32_t run_cg_fused(cola_op_s* op, const SysInfo& s, int nrhs, float* x, float*
     if (last >= 0) HIP_TRY(hipEventSynchronize(op->fused_done[last & 1]));
     uint32_t timed_out = 0;
     HIP_TRY(hipMemcpy(&timed_out, a.err, sizeof(uint32_t), hipMemcpyDeviceToHost));
-    if (timed_out) {
-        op->use_fused = false;         // a group never met: report it and stop using the path
-        return COLA_ERR_HIP;
+    if (timed_out) {                   // a group never met: stop using the path
+        op->use_fused = false;
+        HIP_TRY(fill_i32((int32_t*)a.err, 0, 1, st));
+        return kFusedTimedOut;
     }
     return COLA_OK;
 }
@@ -1047,9 +1053,8 @@ int32_t run_pcg(cola_op_s* op, const SysInfo& s, const double* B, double* X, int
     return COLA_OK;
 }
 
-int32_t solve_system(cola_op_s* op, const SysInfo& s, const double* B, double* X, int nrhs,
-                     const cola_solve_opts* o, cola_solve_info* info, hipStream_t st) {
-    TraceRange trace_range("solve_system");
+int32_t solve_once(cola_op_s* op, const SysInfo& s, const double* B, double* X, int nrhs, const cola_solve_opts* o,
+                   cola_solve_info* info, hipStream_t st) {
     Workspace& w = op->ws;
     const int64_t n = s.n;
     const int ps = (int)w.part_stride;
@@ -1142,6 +1147,16 @@ int32_t solve_system(cola_op_s* op, const SysInfo& s, const double* B, double* X
     }
     if (info) HIP_TRY(write_info(info, w.outer, nullptr, nrhs, st));
     return COLA_OK;
+}
+
+int32_t solve_system(cola_op_s* op, const SysInfo& s, const double* B, double* X, int nrhs,
+                     const cola_solve_opts* o, cola_solve_info* info, hipStream_t st) {
+    TraceRange trace_range("solve_system");
+    int32_t rc = solve_once(op, s, B, X, nrhs, o, info, st);
+    // the separate kernels take the solve from its start: X is written only at the end, or (restarted
+    // refinement) by whole sweeps, each a better start
+    if (rc == kFusedTimedOut) rc = solve_once(op, s, B, X, nrhs, o, info, st);
+    return rc;
 }
 
 void free_resident(cola_op_s* op) {
@@ -1942,6 +1957,12 @@ int32_t cola_op_set_engine(cola_op_t op, int32_t engine, int32_t enable) {
     }
     (void)hipDeviceSynchronize();
     destroy_graphs(op);              // captured chunks embed the previous choice
+    return COLA_OK;
+}
+
+int32_t cola_internal_fused_spin_limit(cola_op_s* op, uint32_t polls) {
+    if (!op) return COLA_ERR_INVALID_ARG;
+    op->fused_spin_limit = polls;
     return COLA_OK;
 }
 

@@ -5,6 +5,8 @@
 
 namespace cola {
 
+constexpr uint32_t kSpinLimit = 1u << 22;  // polls of a barrier wait (seconds)
+
 // One launch runs up to `iters` CG iterations for `nrhs` right-hand sides of
 // one system K1 (x) K2 (x) K3 + diag(d) + sigma2 I.  Every
 // right-hand side is owned by a group of `bpr` co-resident blocks that meet at
@@ -24,6 +26,7 @@ struct FusedCgArgs {
     CgState* cg;         // right-hand side g at cg[g]
     double* slots;       // 3 * nrhs * bpr barrier slots, all bits set at launch
     uint32_t* err;       // set to 1 when a barrier wait times out
+    uint32_t spin_limit; // polls of a barrier wait before that
     SolveCounters* cnt;
 };
 

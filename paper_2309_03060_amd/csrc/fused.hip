@@ -39,7 +39,6 @@ constexpr int D = 64;                      // mode size
 constexpr int PD = D + 4;                  // LDS row pitch (floats)
 constexpr int kFT = 1024;                  // threads per block: 4 quads of 4 waves
 constexpr int kSC1 = 16;                   // cache-policy operand: agent-coherent access
-constexpr uint32_t kSpinLimit = 1u << 22;  // barrier polls before a time-out (seconds)
 
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
@@ -131,8 +130,8 @@ __device__ inline void group_post(double v, double* gslots, int bpr, int rank, u
 // (the same total in every block).  Loads issued since the post stay in
 // flight.  Returns false in every thread after a time-out (the flag is set;
 // the launch is then void).
-__device__ inline bool group_gather(double* gslots, int bpr, int rank, uint32_t k, uint32_t* err, double* s_tot,
-                                    int* s_ok) {
+__device__ inline bool group_gather(double* gslots, int bpr, int rank, uint32_t k, uint32_t spin_limit,
+                                    uint32_t* err, SolveCounters* cnt, double* s_tot, int* s_ok) {
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         const double* set = gslots + (k % 3) * bpr;
@@ -142,8 +141,12 @@ __device__ inline bool group_gather(double* gslots, int bpr, int rank, uint32_t 
             v = lane < bpr ? load_coherent(set + lane) : 0.0;
             const bool ready = lane >= bpr || __builtin_bit_cast(uint64_t, v) != kSlotEmpty;
             if (__all(ready)) break;
-            if (spins > kSpinLimit) {
-                if (lane == 0) __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (spins > spin_limit) {
+                if (lane == 0) {
+                    __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    // the host, which reads this count, launches no further chunk
+                    __hip_atomic_store(&cnt->num_active, -(1 << 30), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
                 ok = 0;
                 break;
             }
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
         if (tid == 0) fs.pending = 0;
         fence_stores();                                        // p and T visible to the group
         group_post(0.0, gslots, a.bpr, rank, k);
-        if (!group_gather(gslots, a.bpr, rank, k++, a.err, &s_tot, &s_ok)) return;
+        if (!group_gather(gslots, a.bpr, rank, k++, a.spin_limit, a.err, a.cnt, &s_tot, &s_ok)) return;
 
         // ---------------- phase B ----------------
         // q = K1 T + (sigma2 + d) p per strip, computed transposed so each lane holds
@@ -447,7 +450,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
                 for (int tj = 0; tj < 2; ++tj)
                     rh[s][ti][tj] = first_of<FULL>(ldc(rsR, olane_of(tj) + 16 * ti, strip_at((u0 + s) * D, tj)),
                                                    ovalid((u0 + s) * D, ti, tj));
-        if (!group_gather(gslots, a.bpr, rank, k++, a.err, &s_tot, &s_ok)) return;
+        if (!group_gather(gslots, a.bpr, rank, k++, a.spin_limit, a.err, a.cnt, &s_tot, &s_ok)) return;
         if (tid == 0) {
             const double pq = s_tot;
             if (!(pq > 0.0) || !finite_d(pq)) {
@@ -484,7 +487,7 @@ __global__ __launch_bounds__(kFT) void k_fused_cg(FusedCgArgs a) {
         fence_stores();                                        // r visible to the group
         group_post(rr_blk, gslots, a.bpr, rank, k);
         load_p(u0);                                            // the next phase A's own data, early
-        if (!group_gather(gslots, a.bpr, rank, k++, a.err, &s_tot, &s_ok)) return;
+        if (!group_gather(gslots, a.bpr, rank, k++, a.spin_limit, a.err, a.cnt, &s_tot, &s_ok)) return;
         if (tid == 0) {
             // convergence, iteration limit and reliable-update request
             const double tot = s_tot;

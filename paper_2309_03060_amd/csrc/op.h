@@ -9,6 +9,7 @@
 
 #include "common.h"
 #include "contract.h"
+#include "fused.h"
 
 namespace cola {
 
@@ -127,6 +128,7 @@ struct cola_op_s {
     bool use_gemm64 = true;         // FP64 passes of two-mode operators with modes multiples of 256: dense FP64 GEMMs
     bool use_fused = true;          // FP32 one-term three-mode operators with modes up to 64: persistent fused CG
     int fused_max_blocks = -1;      // co-resident fused-CG blocks (-1: not yet queried)
+    uint32_t fused_spin_limit = cola::kSpinLimit;   // polls of a group barrier before a time-out
     double* slq_buf = nullptr;      // SLQ: CG coefficient history and per-probe estimates
     size_t slq_elems = 0;
     double* fused_slots = nullptr;      // fused-CG barrier slots (3 * fused_max_blocks), then the time-out flag
@@ -172,3 +174,7 @@ int32_t ensure_workspace(cola_op_s* op, int nrhs, hipStream_t st);
 int32_t dev_alloc(cola_op_s* op, void** p, size_t bytes);
 void dev_free(cola_op_s* op, void* p);
 }
+
+// Not part of the library's interface (the header does not declare it): tests of the time-out lower the
+// polls of a group barrier, so that a group gives up while all of its blocks still leave the launch.
+extern "C" int32_t cola_internal_fused_spin_limit(cola_op_s* op, uint32_t polls);

@@ -25,3 +25,35 @@ def test_route_by_host_checks(dims, every, fused):
     rr = kron.relres(s.factors, unpack(X, [s], 8)[0], B, s.sigma2)
     assert all(i["status"] == 0 for i in infos(info, 8)) and np.all(rr <= 1e-6), rr
     op.close()
+
+
+@pytest.mark.parametrize("refine", ["reliable", "restart"])
+@pytest.mark.parametrize("warm", [False, True])
+def test_time_out_falls_back(refine, warm):
+    """A group barrier that gives up (its polls limited to one; every block still leaves the launch) hands
+    the solve to the separate kernels, and so do the solves that follow."""
+    import ctypes
+    import torch
+    from gpu_util import infos, make_op, pack, unpack
+    rng = np.random.default_rng(11)
+    dims, nrhs = (48, 40, 56), 8
+    s = wl.System(factors=[[wl.wishart_factor(rng, m, shift=0.3) for m in dims]], sigma2=0.2, diag=None)
+    B = rng.standard_normal((nrhs, s.n))
+    op = make_op([s], prec="fp32")
+    op.lib.cola_internal_fused_spin_limit.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
+    assert op.lib.cola_internal_fused_spin_limit(op.handle, 1) == 0
+    op.profile_enable(True)
+    kw = dict(tol=1e-9, max_iters=2000, inner_tol=0.1, refine=refine)
+    if warm:
+        kw["x0"] = pack([0.1 * B])
+    launches = []
+    for _ in range(2):
+        X, info = op.solve(pack([B]), nrhs, **kw)
+        torch.cuda.synchronize()
+        launches.append(op.profile_read("cg_fused")[1])
+        assert op.profile_read("contract_last")[1] > 0
+        rr = kron.relres(s.factors, unpack(X, [s], nrhs)[0], B, s.sigma2)
+        assert all(i["status"] == 0 for i in infos(info, nrhs)) and np.all(rr <= 1e-9), rr
+    # a chunk or two before the host knew, and the second solve does not try the engine again
+    assert 1 <= launches[0] <= 2 and launches[1] == launches[0], launches
+    op.close()
