@@ -907,12 +907,12 @@ COPY_REF_WORDS = 64 << 20            # the counters run's reference copy: 256 Mi
 PMC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 COUNTERS_C2_ITERS = 32               # c2 counters run: one fused launch of 32 iterations x 32 RHS
 KERNEL_SOURCES = {                   # files each launch class is compiled from (counters go stale with them)
-    "contract": ["contract.hip", "contract.h", "common.h"],
+    "contract": ["contract.hip", "contract.h", "modepass.hip", "modepass.h", "modeslice.h", "common.h"],
     "slab23": ["slab.hip", "slab.h", "common.h"],
     "update": ["vector.hip", "vector.h", "common.h"],
     "cg_fused": ["fused.hip", "fused.h", "common.h"],
-    "gemm3": ["gemm3.hip", "gemm3.h", "common.h"],
-    "gemm2": ["gemm.hip", "gemm.h", "common.h"],
+    "gemm3": ["gemm3.hip", "gemm3.h", "contract.h", "common.h"],
+    "gemm2": ["gemm.hip", "gemm.h", "contract.h", "common.h"],
 }
 # bench launch-class name of each counter class, per workload (c2 fuses modes 2 and 3 in the slab pass,
 # so its only column-layout FP32 contraction is the last mode; the fused persistent CG replaces all three)
