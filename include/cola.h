@@ -350,12 +350,11 @@ int32_t cola_autotune_import(cola_op_t op, const char* text);
 #define COLA_ENGINE_FUSED_CG 1  /* persistent CG, one cooperative launch per chunk of iterations:
                                    one-term K1 (x) K2 (x) K3 (+ diag) with modes of up to 64, FP32
                                    working precision, no residual history, where it is the faster
-                                   one (64-wide modes; small ones; enough right-hand sides).  With
-                                   check_every = 0 only 64-wide modes take it: every chunk of 128
-                                   iterations is enqueued up front (capture-safe); a barrier
-                                   time-out, which a captured launch can meet if other work shares
-                                   the GPU, is then reported as COLA_ERR_HIP in every right-hand
-                                   side's info                                               */
+                                   one (64-wide modes; small ones; enough right-hand sides).  With check_every
+                                   = 0 every chunk (128 iterations with 64-wide modes, else 32) is enqueued up front
+                                   (capture-safe); a barrier time-out, which a captured launch
+                                   can meet if other work shares the GPU, is then reported
+                                   as COLA_ERR_HIP in every right-hand side's info          */
 #define COLA_ENGINE_GEMM2    2  /* dense-GEMM MVM: BF16, two-mode, modes multiples of 256       */
 #define COLA_ENGINE_GEMM3    3  /* dense-GEMM MVM: FP32 or BF16x3, one-term three-mode, 256-wide
                                    modes                                                     */

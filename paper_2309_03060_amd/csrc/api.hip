@@ -653,11 +653,8 @@ bool capturing(hipStream_t st) {
 }
 
 bool fused_eligible(const cola_op_s* op, const SysInfo& s, int prec, int check_every, int nrhs) {
-    // the persistent kernel runs its own vector update, which records no residual history.  Without host
-    // checks (a solve that the caller may capture) only 64-wide modes take it: a replay beside other work may
-    // meet a barrier time-out, which nobody is there to answer, and the separate kernels know none.
-    const bool full = s.dims[0] == 64 && s.dims[1] == 64 && s.dims[2] == 64;
-    return op->use_fused && (check_every > 0 || (check_every == 0 && full)) && op->fused_max_blocks != 0 && prec == op->prec && !op->ws.rh.data &&
+    // the persistent kernel runs its own vector update, which records no residual history
+    return op->use_fused && check_every >= 0 && op->fused_max_blocks != 0 && prec == op->prec && !op->ws.rh.data &&
            fused_cg_supported(prec, s.Fv, s.J, s.dims) && fused_cg_pays(s.dims, nrhs, op->fused_max_blocks);
 }
 
@@ -669,7 +666,7 @@ constexpr int32_t kFusedTimedOut = -1000;
 // every chunk of check_every iterations is one cooperative launch per batch of
 // right-hand sides (then the reliable-update tail), with the host reading the
 // count of active right-hand sides one chunk behind, as in the graph path.
-// check_every == 0: every chunk (128 iterations between reliable updates) is
+// check_every == 0: every chunk (128 or 32 iterations between reliable updates) is
 // enqueued up front with no host wait, so the caller may capture the solve;
 // groups that are no longer active leave a launch at once, and a barrier
 // time-out is reported per right-hand side instead of by a host check.
@@ -677,7 +674,10 @@ int32_t run_cg_fused(cola_op_s* op, const SysInfo& s, int nrhs, float* x, float*
                      int check_every, const ReliableTail* tail, hipStream_t st) {
     Workspace& w = op->ws;
     const bool host_checks = check_every > 0;
-    const int chunk = host_checks ? std::min(check_every, max_iters) : (tail ? std::min(128, max_iters) : max_iters);
+    // between reliable updates without host checks: 128 iterations with 64-wide modes, else the 32 of run_cg
+    const bool full = s.dims[0] == 64 && s.dims[1] == 64 && s.dims[2] == 64;
+    const int chunk = host_checks ? std::min(check_every, max_iters)
+                                  : (tail ? std::min(full ? 128 : 32, max_iters) : max_iters);
     const int nchunks = (max_iters + chunk - 1) / chunk;
     const FusedShape shape = fused_cg_shape(s.dims, nrhs, op->fused_max_blocks);
     const int bpr = shape.bpr;
