@@ -5,8 +5,11 @@
 // eigenvalues lam1 (x) .. (x) lamF + sigma2 (the Kronecker eigenvalue rule of
 // the paper's appendix on Kronecker products).  The factors are decomposed
 // here with one-sided (Hestenes) Jacobi in FP64: columns of U = A V are
-// orthogonalised pairwise by plane rotations accumulated into V.  All n/2
-// pairs of one round-robin step are independent, one workgroup each.
+// orthogonalised pairwise by plane rotations accumulated into V, all n/2 pairs of
+// one round-robin step at a time.  Factors of up to 140 points are decomposed side
+// by side: one workgroup per factor holds U in LDS and runs a whole sweep per launch
+// (16 lanes a pair), and the next launch applies the sweep's rotations to the rows of
+// Q.  Larger factors take one launch per step and one workgroup per pair.
 #include "eig.h"
 
 #include <algorithm>

@@ -1,9 +1,9 @@
 // Persistent fused CG for one-term three-mode FP32 operators with modes of up to 64.
 //
-// The separate-kernel path runs three launches per CG iteration (modes 2 and 3
-// of the Kronecker MVM per slab, mode 1 with the direction update, the vector
-// update) and moves q = A p through memory.  Here one cooperative launch runs
-// many iterations.  Right-hand side g is owned by a group of `bpr` blocks that
+// The separate-kernel path runs three or four launches per CG iteration (modes 2
+// and 3 of the Kronecker MVM, in one pass over 64 x 64 slabs or one pass each, mode 1
+// with the direction update, the vector update) and moves q = A p through memory.
+// Here one cooperative launch runs many iterations.  Right-hand side g is owned by a group of `bpr` blocks that
 // only ever exchange data with each other, so they meet at group barriers
 // rather than grid-wide ones; each iteration has three phases:
 //
@@ -19,7 +19,7 @@
 // the old p anyway (and to the end of the launch for the last iteration), so
 // only q has to stay in registers.  Bytes per element and iteration: A reads
 // r, p, x and writes p, T, x (24); B reads T, p (8); C reads and writes r (8):
-// 40 against 56 for the separate kernels.  Data crossing blocks (p, T, r, the partial sums) is
+// 40 against 56 for three separate kernels.  Data crossing blocks (p, T, r, the partial sums) is
 // written and read with agent-coherent accesses (the cache-policy bit that
 // the memory model uses for agent-scope atomics), so a barrier needs no cache
 // write-back.  Each group barrier carries the block's part of the next group

@@ -3,8 +3,9 @@
 // For a term K1 (x) K2 (x) K3 and X = x.reshape(n1, n2, n3), the mode-2 and
 // mode-3 products act on each n2 x n3 slab X[i1] independently:
 // T[i1] = K2 X[i1] K3^T (the per-mode evaluation behind the Kronecker MVM
-// cost of Table 2).  For slabs of 64 x 64 both products are done in LDS: the slab is read once, the intermediate product never
-// leaves the CU, and T is written once.  Blocks are persistent over a range
+// cost of Table 2).  For slabs of 64 x 64 both products are done in LDS: the
+// slab is read once, the intermediate product never leaves the CU, and T is
+// written once.  Blocks are persistent over a range
 // of slabs so the two factors are staged in LDS once per block, and the next
 // slab's loads are issued while the current one is being multiplied.
 #include "slab.h"
