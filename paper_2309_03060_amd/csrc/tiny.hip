@@ -8,9 +8,9 @@
 // for four products, k upwards); what is left is the chain of one load from memory and one LDS loop
 // and barrier per mode, which more threads do not shorten.
 //
-// 12 x 10 x 14, FP32, calls back to back: 1 right-hand side 10.2 -> 8.0 us (6.3 on the GPU, the rest
-// is the call), 64 16.0 -> 7.9, 512 70.8 -> 8.9; 8 x 8 x 8, four terms, FP64: 13.8 -> 8.1 us, 64
-// right-hand sides 60 -> 8.1.
+// 12 x 10 x 14, FP32, calls back to back: 1 right-hand side 10.2 -> 6.4 us (6.3 on the GPU), 64 16.0 -> 6.8,
+// 512 70.8 -> 9.0; 8 x 8 x 8, four terms, FP64: 13.8 -> 7.1 us, 64 right-hand sides 60 -> 7.5 (two
+// of these microseconds are the call's, which lost them by itself).
 #include "tiny.h"
 
 namespace cola {
