@@ -85,8 +85,6 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, lr = lane & 15, lq = lane >> 4;
     const int nk = a.nk;
-    const int ns = (nk + KT - 1) / KT;                       // k slices per term
-    const int steps = ns * a.nsum;
 
     uint32_t L = xcd_order(blockIdx.x, total);
     int64_t g = 0, m0, n0;
@@ -126,7 +124,8 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     const int arow0 = sl.row(tid, 0), akc = sl.row_k(tid);   // k-contiguous vector q: row arow0 + q RQ
     const int bk0 = sl.panel_k(tid, 0), bn = sl.panel_col(tid);          // panel vector q: k bk0 + q PQ
     const int64_t x_end = sl.x_end(GENERAL ? 1 : VW), x_end_last = sl.x_end_last(GENERAL ? 1 : VW);
-    const int64_t xstep = sl.x_step();
+    const int64_t xstep = sl.x_step(), to_last = sl.x_to_last();
+    const int steps = sl.slices() * a.nsum;                  // k slices of all terms
     uint32_t xoff[XV], xlast[XV], foff[FV];
 #pragma unroll
     for (int q = 0; q < XV; ++q) {
@@ -141,7 +140,7 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
         for (int q = 0; q < AV; ++q) beta[q] = a.cg[rhs_of(a, m0 + sl.row_at(sl.row(tid, q), m0, a.G))].beta;
     }
     const bool tail = sl.x_clamped();                        // some vector of the last slice was read early
-    const int idle = (int)(-sl.x_idle() * ES);               // bytes before the last slice's base
+    const bool idle = sl.x_idle_early();
 
     struct Slice { Vec a[AV], r[PNEW ? AV : 1], b[BV]; };
     auto ldv = [&](const char* base, uint32_t off) -> Vec { return *(const VecU*)(base + off); };
@@ -159,8 +158,8 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
     const char* Rl = (const char*)((const V*)a.R + t0 * a.x_tstride + sl.x_base());
     int kl = 0, left = steps;
     auto load_slice = [&](Slice& v) {
-        // past the last slice every lane loads one address (nothing uses it)
-        const uint32_t keep = left > 0 ? 0xffffffffu : 0u;
+        // past the last slice every lane loads one address, or the last slice again (nothing uses it)
+        const uint32_t keep = left > 0 || !idle ? 0xffffffffu : 0u;
         const bool last = kl == k_last;
         auto& vx = [&]() -> auto& { if constexpr (ROWS) return v.a; else return v.b; }();
         auto& vf = [&]() -> auto& { if constexpr (ROWS) return v.b; else return v.a; }();
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
             for (int q = 0; q < FV; ++q)
                 vf[q] = *(const VecU*)((const V*)Fl + (left > 0 ? sl.f_at(tid, q) : 0));
         } else {
-            const int back = left > 0 ? (last ? VW * ES : 0) : idle;
+            const int back = last ? VW * ES : 0;
 #pragma unroll
             for (int q = 0; q < XV; ++q) {
                 const uint32_t o = (last ? xlast[q] : xoff[q]) & keep;
@@ -194,8 +193,8 @@ __global__ __launch_bounds__(kThreads, mode_waves(WM, WN)) void k_mode(PassArgs 
             if constexpr (PNEW) Rl += xstep * ES;
         } else {                                             // the next term
             Fl += (a.k_tstride - k_last) * ES;
-            Xl += (a.x_tstride - (int64_t)(ns - 1) * xstep) * ES;
-            if constexpr (PNEW) Rl += (a.x_tstride - (int64_t)(ns - 1) * xstep) * ES;
+            Xl += (a.x_tstride - to_last) * ES;
+            if constexpr (PNEW) Rl += (a.x_tstride - to_last) * ES;
             kl = 0;
         }
     };

@@ -25,8 +25,8 @@ namespace cola {
 //         too small for that is left to the element-wise variant (mode_needs_general).
 //   the last slice  rows beyond nk repeat row nk - 1, and a vector past the input's end is read early, at
 //         the input's last vector (the kernel puts its elements back in place).
-//   after the last slice  every lane loads one vector, at the last slice's base or, where that is nearer
-//         to the end than a vector, at the input's last vector.
+//   after the last slice  every lane loads one vector, just before the last slice's base (which may be
+//         nearer to the input's end than a vector), or the last slice again where the input starts there.
 // Factor vectors may run past the end of their matrix by part of a slice (the factor buffers are padded
 // by a slice's 128 bytes).
 template <int VW, int KT, int WM, int WN, bool ROWS>
@@ -41,8 +41,8 @@ struct ModeSlices {
     int64_t B, G;                                            // B: COLS only
     int64_t m0, n0, g;                                       // g: COLS only
 
-    COLA_HD int slices() const { return (nk + KT - 1) / KT; }
-    COLA_HD int k_last() const { return (slices() - 1) * KT; }          // first k of the last slice
+    COLA_HD int slices() const { return (int)((uint32_t)(nk + KT - 1) / KT); }
+    COLA_HD int k_last() const { return (int)((uint32_t)(nk - 1) / KT * KT); }         // first k of the last slice
     // vector q of a thread: in a k-contiguous row (row of the tile, k of the slice), in a panel (k, column)
     COLA_HD int row(int tid, int q) const { return tid / RV + q * RQ; }
     COLA_HD int row_k(int tid) const { return tid % RV * VW; }
@@ -59,7 +59,8 @@ struct ModeSlices {
     COLA_HD int64_t x_base() const { return ROWS ? m0 * nk : g * nk * B + n0; }
     COLA_HD int64_t x_step() const { return ROWS ? KT : (int64_t)KT * B; }
     COLA_HD int64_t x_end(int width) const { return (ROWS ? G * nk : G * nk * B) - width - x_base(); }
-    COLA_HD int64_t x_end_last(int width) const { return x_end(width) - (int64_t)(slices() - 1) * x_step(); }
+    COLA_HD int64_t x_to_last() const { return k_last() * (ROWS ? 1 : B); }      // to the last slice's base
+    COLA_HD int64_t x_end_last(int width) const { return x_end(width) - x_to_last(); }
 
     // vector q in a slice before the last
     COLA_HD int64_t x_at(int tid, int q) const {
@@ -81,11 +82,10 @@ struct ModeSlices {
     COLA_HD bool x_clamped() const {
         return x_end_last(VW) < (ROWS ? (int64_t)(MT - 1) * nk + KT : (int64_t)(nk - 1 - k_last()) * B + NT);
     }
-    // the load after the last slice
-    COLA_HD int64_t x_idle() const {
-        const int64_t e = x_end_last(VW);
-        return e < 0 ? e : 0;
-    }
+    // the load after the last slice: from a vector before that slice's base, or the last slice's own again
+    // where that is before the input (x_idle_at for the thread and vector it is asked for)
+    COLA_HD bool x_idle_early() const { return x_base() + x_to_last() >= VW; }
+    COLA_HD int64_t x_idle_at(int tid, int q) const { return x_idle_early() ? -VW : x_last(tid, q); }
     // the factor: vector q from row n0 (ROWS) or m0 (COLS) on
     COLA_HD int64_t f_at(int tid, int q) const {
         return row_at(row(tid, q), ROWS ? n0 : m0, nk) * nk + row_k(tid);

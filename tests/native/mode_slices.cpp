@@ -42,6 +42,7 @@ static void check(int nk, long B, long G) {
                                 fail("moved", VW, KT, S::NT, nk, B, G, s.x_at(tid, q), k * B + c);
                         }
                         in("last slice", last + s.x_last(tid, q));
+                        in("after the last slice", last + s.x_idle_at(tid, q));
                         const long early = s.x_last_wanted(tid, q) - s.x_last(tid, q);
                         if (early > 0 && !s.x_clamped()) fail("not put back", VW, KT, S::NT, nk, B, G, early, 0);
                     }
@@ -51,7 +52,6 @@ static void check(int nk, long B, long G) {
                         if (f < 0 || f + VW > (long)nk * nk + pad) fail("factor", VW, KT, S::MT, nk, B, G, f, nk * nk);
                     }
                 }
-                in("after the last slice", last + s.x_idle());
             }
 }
 
